@@ -55,13 +55,10 @@ ALG_BYTES_PER_PARTICLE = {
 ALG_BYTES_PER_NODE = {"p2g": 16, "g2p": 12, "grid": 16 + 12, "g2p_adj": 12 + 12, "p2g_adj": 16,
                       "grid_adj": 16 + 12 + 16, "g2p2g": 28, "adj_pair": 56}
 
-# kernel symbol of each class for the library's batched variants
-KERNEL_SYMBOL = {"p2g": {0: "k_p2g_direct", 1: "k_p2g_lds", 2: "k_p2g_seg", 3: "k_p2g_pull"},
-                 "g2p": {0: "k_g2p_direct", 1: "k_g2p_lds"},
-                 "g2p_adj": {0: "k_g2p_adjoint_direct", 1: "k_g2p_adjoint_lds", 2: "k_g2p_adjoint_seg",
-                             3: "k_g2p_adjoint_pull"},
-                 "p2g_adj": {0: "k_p2g_adjoint_direct", 1: "k_p2g_adjoint_lds"},
-                 "g2p2g": {1: "k_g2p2g", 2: "k_g2p2g_pull"}, "adj_pair": {1: "k_adj_pair"}}
+# kernel symbol of each class for the library's batched variants: with the column scatter, and with global atomics
+KERNEL_SYMBOL = {"p2g": ("k_p2g_col", "k_p2g_direct"), "g2p": ("k_g2p", "k_g2p"),
+                 "g2p_adj": ("k_g2p_adjoint_col", "k_g2p_adjoint_direct"), "p2g_adj": ("k_p2g_adjoint",) * 2,
+                 "g2p2g": ("k_g2p2g_col",) * 2, "adj_pair": ("k_adj_pair_col", "k_adj_pair_col")}
 OPTION_NAMES = ("P2G", "G2P", "G2P_ADJ", "P2G_ADJ", "MIN_RUN", "GRID_CAP", "MAX_RUN", "BOX", "SPECIALIZE", "FUSE",
                 "FUSE_ADJ", "XCD", "GRID_LIST")
 
@@ -69,28 +66,20 @@ OPTION_NAMES = ("P2G", "G2P", "G2P_ADJ", "P2G_ADJ", "MIN_RUN", "GRID_CAP", "MAX_
 def kernel_source_sha() -> str:
     import hashlib
     h = hashlib.sha256()
-    for f in ("mpm_device.h", "mpm_kernels.h", "mpm_kernels.hip", "mpm_kernels_lds.hip"):
+    for f in ("mpm_device.h", "mpm_kernels.h", "mpm_kernels.hip", "mpm_kernels_col.hip"):
         with open(os.path.join(ROOT, "paper_2412_12089_amd", "csrc", f), "rb") as fh:
             h.update(fh.read())
     return h.hexdigest()[:16]
 
 
-def kernel_instance(symbol: str, variant, tuned: dict, envs) -> str:
-    """Name of the launched instantiation, as profilers print it: the LDS-staged
-    kernels are templates over (persistent grid, LDS box nodes, material)."""
-    if not variant:
+def kernel_instance(symbol: str, tuned: dict, envs) -> str:
+    """Name of the launched instantiation, as profilers print it: templates over
+    ([LDS box nodes,] material; -1 reads it at run time)."""
+    if symbol.endswith("_direct"):
         return symbol
     mats = sorted({e.material for e in envs})
     mat = mats[0] if tuned["SPECIALIZE"] and len(mats) == 1 else -1
-    if symbol == "k_g2p2g_pull":   # no persistent-grid parameter, the pull box budgets
-        return f"{symbol}<{1024 if tuned['BOX'] else 2048}, {mat}>"
-    if symbol in ("k_g2p2g", "k_adj_pair"):   # no persistent-grid parameter
-        return f"{symbol}<{384 if tuned['BOX'] else 1024}, {mat}>"
-    n_items = sum(-(-e.n_particles // 256) for e in envs)
-    persist = "true" if 0 < tuned["GRID_CAP"] < n_items else "false"
-    if symbol.endswith("_pull"):   # the pull scatters' larger box budgets
-        return f"{symbol}<{persist}, {1024 if tuned['BOX'] else 2048}, {mat}>"
-    return f"{symbol}<{persist}, {384 if tuned['BOX'] else 1024}, {mat}>"
+    return f"{symbol}<{384 if tuned['BOX'] else 1024}, {mat}>" if symbol.endswith("_col") else f"{symbol}<{mat}>"
 
 
 def measured_traffic(workload: str, symbol: str):
@@ -430,10 +419,7 @@ def main():
         (mf, nf), (mb, nb) = kt_f[k], kt_b[k]
         n = nf + nb
         kt[k] = ((mf * nf + mb * nb) / n if n else 0.0, n)
-    variant = {"p2g": b.get_option(_capi.OPT_P2G), "g2p": b.get_option(_capi.OPT_G2P),
-               "g2p_adj": b.get_option(_capi.OPT_G2P_ADJ), "p2g_adj": b.get_option(_capi.OPT_P2G_ADJ),
-               "g2p2g": b.get_option(_capi.OPT_FUSE) * (2 if b.get_option(_capi.OPT_P2G) == 3 else 1),
-               "adj_pair": b.get_option(_capi.OPT_FUSE_ADJ)}
+    direct = {"p2g": b.get_option(_capi.OPT_P2G) == 0, "g2p_adj": b.get_option(_capi.OPT_G2P_ADJ) == 0}
     mem = b.memory_bytes()
     b.close()
     nodes = touched_nodes(envs)
@@ -442,7 +428,7 @@ def main():
     dom_ms = kt[dom][0]
     alg_bytes = ALG_BYTES_PER_PARTICLE[dom] * N + ALG_BYTES_PER_NODE.get(dom, 0) * nodes
     achieved = alg_bytes / (dom_ms * 1e-3) / 1e9
-    symbol = kernel_instance(KERNEL_SYMBOL.get(dom, {}).get(variant.get(dom), dom), variant.get(dom), tuned, envs)
+    symbol = kernel_instance(KERNEL_SYMBOL[dom][direct.get(dom, False)], tuned, envs) if dom in KERNEL_SYMBOL else dom
     traffic = measured_traffic(wl.name, symbol)
     # whole step against the method's bytes: 672 B per particle-substep fwd+bwd, 96/K B of
     # checkpoints, 28 + 56 B per touched node and substep

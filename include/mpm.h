@@ -313,31 +313,23 @@ int mpm_backward(mpm_batch* b, const float* gx, const float* gv, const float* gC
 /* Execution options (mpm_set_option / mpm_get_option). Changing a kernel
  * variant drops the cached graphs. */
 #define MPM_OPT_GRAPHS 1       /* 1: replay each segment as a hipGraph (batched mode only; default 1) */
-#define MPM_OPT_P2G 2          /* P2G variant: 0 global atomics, 1 LDS-staged, 2 LDS + per-cell runs (default),
-                                  3 LDS pull: each LDS box node summed by its owner thread from the block's
-                                  particles (counting-sorted by cell in LDS), no LDS float atomics */
-#define MPM_OPT_G2P 3          /* G2P variant: 0 global gathers, 1 LDS-staged (default) */
-#define MPM_OPT_G2P_ADJ 4      /* G2P adjoint: 0 global atomics, 1 LDS-staged, 2 LDS + per-cell runs (default),
-                                  3 LDS pull (as MPM_OPT_P2G = 3) */
-#define MPM_OPT_P2G_ADJ 5      /* P2G adjoint: 0 global gathers, 1 LDS-staged (default) */
-#define MPM_OPT_MIN_RUN 6      /* per-cell-run variants engage when particles per stencil base >= this (default 3) */
-#define MPM_OPT_GRID_CAP 7     /* LDS-staged kernels: 0 = one block per work item (default); > 0 = a persistent
-                                  grid of this many blocks striding over the work items */
-#define MPM_OPT_MAX_RUN 8      /* per-cell-run variants cut a run of one stencil base every this many particles
-                                  (default 8) */
-#define MPM_OPT_BOX 9          /* LDS-staged kernels' box budget: 0 = 1024 grid nodes per block (default),
-                                  1 = 384 nodes (less LDS, more blocks per CU; a block whose box is larger
-                                  falls back to global atomics) */
-#define MPM_OPT_FUSE 11        /* 1: within a segment, G2P of substep k and the P2G of substep k + 1 run as
-                                  one kernel (the new state is scattered from registers); needs
-                                  MPM_OPT_P2G = 2 (per-cell runs) or 3 (pull), otherwise ignored. Default 0;
-                                  the autotuner may set it */
-#define MPM_OPT_FUSE_ADJ 12    /* 1: within a segment's backward, the P2G adjoint of substep k and the G2P
-                                  adjoint of substep k - 1 run as one kernel (the cotangent of state k stays
-                                  in registers; the G2P adjoint part is the pull scatter when
-                                  MPM_OPT_G2P_ADJ = 3, else the segment-reduced one). Batched mode.
-                                  Default 0; the autotuner may set it */
-#define MPM_OPT_XCD 13         /* LDS-staged kernels: 1 = each launch's work items are ordered so that the
+#define MPM_OPT_P2G 2          /* P2G: 0 one thread per particle, global atomics; 1, 2 (default) and 3: sums per
+                                  column of base cells in LDS, one global atomic per block, node and channel */
+#define MPM_OPT_G2P 3          /* 0 or 1 (default): the same kernel, gathers straight from the grid */
+#define MPM_OPT_G2P_ADJ 4      /* G2P adjoint: as MPM_OPT_P2G (its scatter of node-velocity cotangents) */
+#define MPM_OPT_P2G_ADJ 5      /* 0 or 1 (default): the same kernel, gathers straight from the grid */
+#define MPM_OPT_MIN_RUN 6      /* 1 .. 256 (default 3), MPM_OPT_GRID_CAP >= 0 (default 0), MPM_OPT_MAX_RUN */
+#define MPM_OPT_GRID_CAP 7     /*   1 .. 256 (default 8): accepted and read back; no kernel depends on them */
+#define MPM_OPT_MAX_RUN 8
+#define MPM_OPT_BOX 9          /* LDS budget of the column sums: 0 = 1024 grid nodes per block and pass (default),
+                                  1 = 384 (less LDS, more blocks per CU; a block with more nodes takes more passes) */
+#define MPM_OPT_FUSE 11        /* 1 (default): within a segment, G2P of substep k and the P2G of substep k + 1 run as
+                                  one kernel (the new state is scattered from registers); needs MPM_OPT_P2G != 0,
+                                  otherwise ignored. 0: two kernels */
+#define MPM_OPT_FUSE_ADJ 12    /* 1 (default): within a segment's backward, the P2G adjoint of substep k and the G2P
+                                  adjoint of substep k - 1 run as one kernel (the cotangent of state k stays in
+                                  registers). Batched mode. 0: two kernels */
+#define MPM_OPT_XCD 13         /* 1 = each launch's work items are ordered so that the
                                   blocks one XCD receives (block i goes to XCD i mod 8) take a contiguous
                                   run of items, keeping an env's grid lines in one XCD's L2; 0 = item
                                   order (default). Results are the same up to float summation order; the
@@ -346,7 +338,7 @@ int mpm_backward(mpm_batch* b, const float* gx, const float* gv, const float* gC
                                   flagged ones with one wave ballot and run only those, instead of one
                                   block per 4 tiles of the whole grid (fewer, busier blocks when few tiles
                                   are flagged). Batched mode. Default 0; the autotuner may set it */
-#define MPM_OPT_SPECIALIZE 10  /* LDS-staged kernels: 1 = one launch per material over that material's work items,
+#define MPM_OPT_SPECIALIZE 10  /* 1 = one launch per material over that material's work items,
                                   compiled for it (default); 0 = one launch over all items, material read at run time */
 
 /* Sets one option; INVALID_ARG for an unknown option or value. */
@@ -355,9 +347,8 @@ int mpm_set_option(mpm_batch* b, int32_t option, int32_t value);
 int mpm_get_option(mpm_batch* b, int32_t option, int32_t* value);
 
 /* Autotuner (batched mode). Runs ckpt_every substeps from the current state
- * with every kernel variant (MPM_OPT_P2G, _G2P, _G2P_ADJ, _P2G_ADJ, _MIN_RUN,
- * _BOX, _SPECIALIZE, _FUSE, _FUSE_ADJ, _XCD, _GRID_CAP, _MAX_RUN), one option
- * at a time. A candidate is kept only if its end
+ * with every kernel variant (MPM_OPT_P2G, _G2P_ADJ, _BOX, _SPECIALIZE, _FUSE,
+ * _FUSE_ADJ, _XCD, _GRID_LIST), one option at a time. A candidate is kept only if its end
  * state (x, v: relative error <= 1e-5) and its initial-state cotangent for an
  * all-ones loss cotangent (<= 1e-4) agree with the one-thread-per-particle
  * kernels; the fastest kept candidate wins, a later one only if it is more

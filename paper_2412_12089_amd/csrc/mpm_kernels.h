@@ -77,58 +77,31 @@ void launch_g2p_adjoint_direct(const float* st, const float* st_next, const floa
 void launch_p2g_adjoint_direct(const float* st, const float* part, float* cot_out, int64_t N, const EnvDev* envs,
                                const WorkItem* items, int n_items, const float* gcot, double* pacc, int k_call, const float* cot_in, hipStream_t s);
 
-// LDS-staged variants of the particle kernels (batched mode). Each launch
-// covers work items of one material `mat`, compiled for that material; `box`
-// picks the LDS box budget (0: 1024 nodes, 1: 384 nodes).
-void launch_p2g_lds(const float* st, int64_t N, const EnvDev* envs, const WorkItem* items, int n_items, float* grid,
-                    uint32_t* flags, int32_t* errs, int k_call, int grid_cap, int box, int mat, hipStream_t s);
-void launch_g2p_lds(const float* st, float* out, int64_t N, const EnvDev* envs, const WorkItem* items, int n_items,
-                    const float* grid, int32_t* errs, int k_call, int grid_cap, int box, int mat, hipStream_t s);
-void launch_g2p_adjoint_lds(const float* st, const float* st_next, const float* cot, float* part, int64_t N, const EnvDev* envs,
-                            const WorkItem* items, int n_items, const float* grid, float* gcot, double* pacc,
-                            int k_call, int grid_cap, int box, int mat, hipStream_t s);
-void launch_p2g_adjoint_lds(const float* st, const float* part, float* cot_out, int64_t N, const EnvDev* envs,
-                            const WorkItem* items, int n_items, const float* gcot, double* pacc, int k_call, const float* cot_in, int grid_cap, int box, int mat, hipStream_t s);
-
-// pull scatters: the LDS-staged kernels' boxes, but each box node is summed by
-// its owner thread from LDS payloads of the block's particles (counting-sorted
-// by stencil base) instead of LDS float atomics
-void launch_p2g_pull(const float* st, int64_t N, const EnvDev* envs, const WorkItem* items, int n_items, float* grid,
-                     uint32_t* flags, int32_t* errs, int k_call, int grid_cap, int box, int mat, hipStream_t s);
-void launch_g2p_adjoint_pull(const float* st, const float* st_next, const float* cot, float* part, int64_t N,
-                             const EnvDev* envs, const WorkItem* items, int n_items, const float* grid, float* gcot,
-                             double* pacc, int k_call, int grid_cap, int box, int mat, hipStream_t s);
-
-// segment-reduced scatters: runs = min_run | max_run << 16. Blocks whose
-// particles average at least min_run per run sum each run (cut at max_run
-// particles) in registers before the LDS atomics
-void launch_p2g_seg(const float* st, int64_t N, const EnvDev* envs, const WorkItem* items, int n_items, float* grid,
-                    uint32_t* flags, int32_t* errs, int runs, int k_call, int grid_cap, int box, int mat, hipStream_t s);
-void launch_g2p_adjoint_seg(const float* st, const float* st_next, const float* cot, float* part, int64_t N, const EnvDev* envs,
-                            const WorkItem* items, int n_items, const float* grid, float* gcot, double* pacc,
-                            int runs, int k_call, int grid_cap, int box, int mat, hipStream_t s);
-
-// G2P of substep k fused with the segment-reduced P2G of substep k + 1
-// (grid_in: substep k's grid, read; grid_out / flags_out: substep k + 1's)
-// G2P of substep k fused with the pull P2G of substep k + 1 (the low particles-per-cell form of launch_g2p2g)
-void launch_g2p2g_pull(const float* st, float* out, int64_t N, const EnvDev* envs, const WorkItem* items, int n_items,
-                       const float* grid_in, float* grid_out, uint32_t* flags_out, int32_t* errs, int k_call, int box,
-                       int mat, hipStream_t s);
-void launch_g2p2g(const float* st, float* out, int64_t N, const EnvDev* envs, const WorkItem* items, int n_items,
-                  const float* grid_in, float* grid_out, uint32_t* flags_out, int32_t* errs, int runs, int k_call,
-                  int box, int mat, hipStream_t s);
-
+// Particle kernels of the batched mode (mpm_kernels_col.hip). Each launch covers
+// work items of one material `mat`, compiled for it (-1: any, read at run
+// time); `box` picks the scatter's LDS box budget (0: 1024 nodes, 1: 384).
+void launch_p2g_col(const float* st, int64_t N, const EnvDev* envs, const WorkItem* items, int n_items, float* grid,
+                    uint32_t* flags, int32_t* errs, int k_call, int box, int mat, hipStream_t s);
+void launch_g2p(const float* st, float* out, int64_t N, const EnvDev* envs, const WorkItem* items, int n_items,
+                const float* grid, int32_t* errs, int k_call, int mat, hipStream_t s);
+void launch_g2p_adjoint_col(const float* st, const float* st_next, const float* cot, float* part, int64_t N,
+                            const EnvDev* envs, const WorkItem* items, int n_items, const float* grid, float* gcot,
+                            double* pacc, int k_call, int box, int mat, hipStream_t s);
+void launch_p2g_adjoint(const float* st, const float* part, float* cot_out, int64_t N, const EnvDev* envs,
+                        const WorkItem* items, int n_items, const float* gcot, double* pacc, int k_call,
+                        const float* cot_in, int mat, hipStream_t s);
+// G2P of substep k fused with the P2G of substep k + 1 (grid_in: substep k's
+// grid, read; grid_out / flags_out: substep k + 1's)
+void launch_g2p2g_col(const float* st, float* out, int64_t N, const EnvDev* envs, const WorkItem* items, int n_items,
+                      const float* grid_in, float* grid_out, uint32_t* flags_out, int32_t* errs, int k_call, int box,
+                      int mat, hipStream_t s);
 // P2G adjoint of substep k fused with the G2P adjoint of substep k - 1 (k_call:
 // substep k's call index; st_prev / st: states k - 1 and k; grid_prev: substep
-// k - 1's grid; gcot: channels 3-6 read, 0-2 scattered into; part: substep k's
+// k - 1's grid; gcot: group 1 read, group 0 scattered into; part: substep k's
 // partials in, substep k - 1's out; cot_end: state-k cotangent of envs frozen at k)
-// P2G adjoint of substep k fused with the pull G2P adjoint of substep k - 1
-void launch_adj_pair_pull(const float* st_prev, const float* st, float* part, const float* cot_end, int64_t N,
-                          const EnvDev* envs, const WorkItem* items, int n_items, const float* grid_prev, float* gcot,
-                          double* pacc, int k_call, int box, int mat, hipStream_t s);
-void launch_adj_pair(const float* st_prev, const float* st, float* part, const float* cot_end, int64_t N,
-                     const EnvDev* envs, const WorkItem* items, int n_items, const float* grid_prev, float* gcot,
-                     double* pacc, int runs, int k_call, int box, int mat, hipStream_t s);
+void launch_adj_pair_col(const float* st_prev, const float* st, float* part, const float* cot_end, int64_t N,
+                         const EnvDev* envs, const WorkItem* items, int n_items, const float* grid_prev, float* gcot,
+                         double* pacc, int k_call, int box, int mat, hipStream_t s);
 
 // per-env weighted moments of caller-order x, v (see mpm_observe.hip) and their VJP
 void launch_moments(const WorkItem* items, int n_items, const EnvDev* envs, const float* x, const float* v,

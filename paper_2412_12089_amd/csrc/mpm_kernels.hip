@@ -440,7 +440,7 @@ __global__ void __launch_bounds__(256) k_p2g_direct(const float* __restrict__ st
 #pragma unroll
         for (int a = 0; a < 3; ++a) {
           const float mv = e.mp * s.v[a] + A.m[a][0] * d[0] + A.m[a][1] * d[1] + A.m[a][2] * d[2];
-          atomicAdd(g + (1 + a) * CH, W * mv);
+          atomicAdd(g + 1 + a, W * mv);
         }
       }
 }
@@ -607,25 +607,24 @@ MD void grid_update_tile(const EnvDev* __restrict__ envs, const int32_t* __restr
   const EnvDev& e = envs[ei];
   int i, j, k;
   node_coords(e, tile, l, i, j, k);
-  float* g = grid + tile * 512 + l;
-  const float m = g[0];
+  float* g = grid + tile * 512 + l * 4;
+  const float4 mP = ld4(g);
+  const float m = mP.x;
   float v[3] = {0.f, 0.f, 0.f};
   if (m > 0.f) {
     const float inv = 1.f / m;
-    v[0] = fmaf(g[CH], inv, e.dt * e.gx);
-    v[1] = fmaf(g[2 * CH], inv, e.dt * e.gy);
-    v[2] = fmaf(g[3 * CH], inv, e.dt * e.gz);
+    v[0] = fmaf(mP.y, inv, e.dt * e.gx);
+    v[1] = fmaf(mP.z, inv, e.dt * e.gy);
+    v[2] = fmaf(mP.w, inv, e.dt * e.gz);
     const int nc = COLS == 0 ? 0 : COLS == 1 ? min(e.n_col, 1) : e.n_col;
 #pragma unroll 1
     for (int ci = 0; ci < nc; ++ci)
       if (e.col[ci].has_collider) collider_blend(e, e.col[ci], motion, t0, clock + ei, k_rel, i, j, k, v);
   }
   if (is_wall(e, i, j, k)) v[0] = v[1] = v[2] = 0.f;
-  g[4 * CH] = v[0];
-  g[5 * CH] = v[1];
-  g[6 * CH] = v[2];
+  st4(g + G1, v[0], v[1], v[2], 0.f);
   if (clear) {
-    g[0] = 0.f; g[CH] = 0.f; g[2 * CH] = 0.f; g[3 * CH] = 0.f;
+    st4(g, 0.f, 0.f, 0.f, 0.f);
     if (l == 0) flags[tile] = 0u;
   }
 }
@@ -748,7 +747,7 @@ MD void collider_blend_adjoint(const EnvDev& e, const ColDev& cd, const float* _
   for (int a = 0; a < 3; ++a) vb[a] = (1.f - c.s) * vb[a] + c.s * ub[a];
 }
 
-// reads vbar (channels 0-2 of gcot), writes mbar (3) and Pbar (4-6), clears
+// reads vbar (group 0 of gcot), writes mbar and Pbar (group 1), clears
 // vbar and the tape grid of this substep (and its flag)
 // one flagged tile (one wave, lane l = node) of the grid adjoint (COLS as for the update)
 template <int COLS>
@@ -760,11 +759,12 @@ MD void grid_adjoint_tile(const EnvDev* __restrict__ envs, const int32_t* __rest
   const EnvDev& e = envs[ei];
   int i, j, k;
   node_coords(e, tile, l, i, j, k);
-  float* g = grid + tile * 512 + l;
-  float* gc = gcot + tile * 512 + l;
-  const float m = g[0];
-  const float P[3] = {g[CH], g[2 * CH], g[3 * CH]};
-  float vb[3] = {gc[0], gc[CH], gc[2 * CH]};   // cotangent of the node velocity
+  float* g = grid + tile * 512 + l * 4;
+  float* gc = gcot + tile * 512 + l * 4;
+  const float4 mP = ld4(g), vb4 = ld4(gc);
+  const float m = mP.x;
+  const float P[3] = {mP.y, mP.z, mP.w};
+  float vb[3] = {vb4.x, vb4.y, vb4.z};   // cotangent of the node velocity
   float mb = 0.f, Pb[3] = {0.f, 0.f, 0.f};
   const bool act = !is_wall(e, i, j, k) && m > 0.f;
   const float inv = act ? 1.f / m : 0.f;
@@ -808,13 +808,10 @@ MD void grid_adjoint_tile(const EnvDev* __restrict__ envs, const int32_t* __rest
     for (int a = 0; a < 3; ++a) Pb[a] = vb[a] * inv;
     mb = -(vb[0] * P[0] + vb[1] * P[1] + vb[2] * P[2]) * inv * inv;
   }
-  gc[3 * CH] = mb;
-  gc[4 * CH] = Pb[0];
-  gc[5 * CH] = Pb[1];
-  gc[6 * CH] = Pb[2];
-  gc[0] = 0.f; gc[CH] = 0.f; gc[2 * CH] = 0.f;
-#pragma unroll
-  for (int c = 0; c < 7; ++c) g[c * CH] = 0.f;
+  st4(gc + G1, mb, Pb[0], Pb[1], Pb[2]);
+  st4(gc, 0.f, 0.f, 0.f, 0.f);
+  st4(g, 0.f, 0.f, 0.f, 0.f);
+  st4(g + G1, 0.f, 0.f, 0.f, 0.f);
   if (l == 0) flags[tile] = 0u;
 }
 
@@ -865,9 +862,9 @@ __global__ void __launch_bounds__(256) k_grid_clear_flagged(int64_t ntiles, floa
   const int l = threadIdx.x & 63;
   if (tile >= ntiles) return;
   if (flags[tile] == 0u) return;
-  float* g = grid + tile * 512 + l;
-#pragma unroll
-  for (int c = 0; c < 8; ++c) g[c * CH] = 0.f;
+  float* g = grid + tile * 512 + l * 4;
+  st4(g, 0.f, 0.f, 0.f, 0.f);
+  st4(g + G1, 0.f, 0.f, 0.f, 0.f);
   if (l == 0) flags[tile] = 0u;
 }
 
@@ -910,8 +907,8 @@ __global__ void __launch_bounds__(256) k_g2p_direct(const float* __restrict__ st
       float col[3] = {0.f, 0.f, 0.f}, colz[3] = {0.f, 0.f, 0.f};
 #pragma unroll
       for (int oz = 0; oz < 3; ++oz) {
-        const float* g = genv + (sa.x[ox] + sa.y[oy] + sa.z[oz]);
-        const float vi[3] = {g[4 * CH], g[5 * CH], g[6 * CH]};
+        const float4 v4 = ld4(genv + (sa.x[ox] + sa.y[oy] + sa.z[oz]) + G1);
+        const float vi[3] = {v4.x, v4.y, v4.z};
         const float W = wxy * sc.w[2][oz], Wd = wxy * wdz[oz];
 #pragma unroll
         for (int a = 0; a < 3; ++a) {
@@ -962,7 +959,7 @@ MD void block_reduce_params(float pb[PB_COUNT], double* __restrict__ acc) {
   }
 }
 
-// G2P adjoint: scatters grid-velocity cotangents (channels 0-2 of gcot) and
+// G2P adjoint: scatters grid-velocity cotangents (group 0 of gcot) and
 // writes the particle's direct x and F cotangents into `part` (12 comps)
 __global__ void __launch_bounds__(256) k_g2p_adjoint_direct(const float* __restrict__ st,
                                                             const float* __restrict__ st_next, const float* __restrict__ cot,
@@ -1006,15 +1003,15 @@ __global__ void __launch_bounds__(256) k_g2p_adjoint_direct(const float* __restr
           const float gW[3] = {e.fn * sc.dw[0][ox] * wy * wz, e.fn * wx * sc.dw[1][oy] * wz, e.fn * wx * wy * sc.dw[2][oz]};
           const float d[3] = {((float)ox - sc.f[0]) * e.dx, ((float)oy - sc.f[1]) * e.dx, ((float)oz - sc.f[2]) * e.dx};
           const int64_t nb = node_base(e, sc.b[0] + ox, sc.b[1] + oy, sc.b[2] + oz);
-          const float* g = grid + nb;
-          const float vi[3] = {g[4 * CH], g[5 * CH], g[6 * CH]};
+          const float4 v4 = ld4(grid + nb + G1);
+          const float vi[3] = {v4.x, v4.y, v4.z};
           float gv[3];
           for (int a = 0; a < 3; ++a)
             gv[a] = vb[a] + D4 * (Cb.m[a][0] * d[0] + Cb.m[a][1] * d[1] + Cb.m[a][2] * d[2]);
           float* gc = gcot + nb;
           atomicAdd(gc, W * gv[0]);
-          atomicAdd(gc + CH, W * gv[1]);
-          atomicAdd(gc + 2 * CH, W * gv[2]);
+          atomicAdd(gc + 1, W * gv[1]);
+          atomicAdd(gc + 2, W * gv[2]);
           const float vg = vi[0] * gv[0] + vi[1] * gv[1] + vi[2] * gv[2];
           for (int a = 0; a < 3; ++a) {
             const float ctv = Cb.m[0][a] * vi[0] + Cb.m[1][a] * vi[1] + Cb.m[2][a] * vi[2];
@@ -1067,9 +1064,9 @@ __global__ void __launch_bounds__(256) k_p2g_adjoint_direct(const float* __restr
           const float W = wx * wy * wz;
           const float gW[3] = {e.fn * sc.dw[0][ox] * wy * wz, e.fn * wx * sc.dw[1][oy] * wz, e.fn * wx * wy * sc.dw[2][oz]};
           const float d[3] = {((float)ox - sc.f[0]) * e.dx, ((float)oy - sc.f[1]) * e.dx, ((float)oz - sc.f[2]) * e.dx};
-          const float* gc = gcot + node_base(e, sc.b[0] + ox, sc.b[1] + oy, sc.b[2] + oz);
-          const float mb = gc[3 * CH];
-          const float Pb[3] = {gc[4 * CH], gc[5 * CH], gc[6 * CH]};
+          const float4 mP = ld4(gcot + node_base(e, sc.b[0] + ox, sc.b[1] + oy, sc.b[2] + oz) + G1);
+          const float mb = mP.x;
+          const float Pb[3] = {mP.y, mP.z, mP.w};
           float mom[3], vcd[3];
           for (int a = 0; a < 3; ++a) {
             const float Ad = A.m[a][0] * d[0] + A.m[a][1] * d[1] + A.m[a][2] * d[2];

@@ -2,7 +2,7 @@
 //
 // A batch holds E environments whose particles are concatenated (CSR by env)
 // in structure-of-arrays FP32 state buffers of 24 components, and whose dense
-// grids are concatenated tile by tile (4^3 nodes, 8 channels). A forward of S
+// grids are concatenated tile by tile (4^3 nodes, two groups of four floats). A forward of S
 // substeps runs in segments of K: each segment sorts the particles by
 // (env, tile, cell) -- the sorted state is the segment's checkpoint -- and
 // then runs its substeps (P2G, grid update, G2P). With recording on, the last
@@ -102,18 +102,17 @@ struct mpm_batch {
   bool last_seg_taped = false;
   std::vector<int32_t> env_err_h;
 
-  // kernel variants of the batched mode (0: one thread per particle with
-  // global atomics, 1: LDS-staged), chosen by mpm_autotune
-  // P2G / G2P adjoint: 2 = LDS-staged with segment reduction for blocks whose
-  // particles average at least min_run per stencil base
-  int var_p2g = 2, var_g2p = 1, var_g2p_adj = 2, var_p2g_adj = 1;
-  int min_run = 3;
-  int max_run = 8;    // runs of one stencil base are split every max_run particles
-  int grid_cap = 0;   // 0: one block per work item; > 0: persistent grid of this many blocks
-  int box = 0;        // LDS box budget of the LDS-staged kernels: 0 = 1024 nodes, 1 = 384 nodes
-  int specialize = 1; // LDS-staged kernels: 1 = one launch per material, compiled for it; 0 = one generic launch
-  int fuse = 0;       // 1: G2P of substep k and P2G of substep k + 1 in one kernel (with the segment P2G)
-  int fuse_adj = 0;   // 1: P2G adjoint of substep k and G2P adjoint of substep k - 1 in one kernel
+  // kernel variants of the batched mode, chosen by mpm_autotune. P2G / G2P
+  // adjoint: 0 = one thread per particle with global atomics, else the column
+  // scatter. The fused schedules are the default: they read the state once per
+  // substep instead of twice, and were the faster ones on every batch timed
+  // (16 to 12,500 blocks, 1 to 8 particles per cell).
+  int var_p2g = 2, var_g2p_adj = 2;
+  int box = 0;        // LDS box budget of the column scatter: 0 = 1024 nodes, 1 = 384 nodes
+  int specialize = 1; // 1 = one launch per material, compiled for it; 0 = one generic launch
+  int fuse = 1;       // 1: G2P of substep k and P2G of substep k + 1 in one kernel
+  int fuse_adj = 1;   // 1: P2G adjoint of substep k and G2P adjoint of substep k - 1 in one kernel
+  int var_g2p = 1, var_p2g_adj = 1, min_run = 3, max_run = 8, grid_cap = 0;   // read back only
   int xcd = 0;        // 1: order each launch's items so that the blocks one XCD receives take a contiguous run
   int grid_list = 0;  // 1 / 2: the grid passes take 64 / 16 tiles per block and run only the flagged ones
   int max_col = 0;     // most colliders an env holds (slots in use): picks the grid passes' compiled variant
@@ -217,7 +216,7 @@ struct Span {
   }
 };
 
-// the (material, first, count) ranges the LDS-staged kernels launch over:
+// the (material, first, count) ranges the particle kernels launch over:
 // one per material, or one generic range (material -1) over all items in env order
 const std::vector<mpm_batch::MatRange>& launch_ranges(mpm_batch* b) {
   if (b->specialize) return b->mat_ranges;
@@ -230,16 +229,12 @@ const std::vector<mpm_batch::MatRange>& launch_ranges(mpm_batch* b) {
 // batched-mode pieces of a substep
 void batched_p2g(mpm_batch* b, const float* in, int gi, int kc) {
   const hipStream_t s = b->stream;
-  const int ni = (int)b->items_h.size();
-  const int runs = b->min_run | (b->max_run << 16);
   Span sp(b, KC_P2G);
-  if (b->var_p2g == 0) launch_p2g_direct(in, b->N, b->envs_d, b->items_d, ni, b->grid[gi], b->flags[gi], b->errs, kc, s);
-  for (const auto& r : launch_ranges(b)) {
-    const WorkItem* it = b->items_mat_d + r.first;
-    if (b->var_p2g == 2) launch_p2g_seg(in, b->N, b->envs_d, it, r.count, b->grid[gi], b->flags[gi], b->errs, runs, kc, b->grid_cap, b->box, r.mat, s);
-    else if (b->var_p2g == 1) launch_p2g_lds(in, b->N, b->envs_d, it, r.count, b->grid[gi], b->flags[gi], b->errs, kc, b->grid_cap, b->box, r.mat, s);
-    else if (b->var_p2g == 3) launch_p2g_pull(in, b->N, b->envs_d, it, r.count, b->grid[gi], b->flags[gi], b->errs, kc, b->grid_cap, b->box, r.mat, s);
-  }
+  if (b->var_p2g == 0)
+    launch_p2g_direct(in, b->N, b->envs_d, b->items_d, (int)b->items_h.size(), b->grid[gi], b->flags[gi], b->errs, kc, s);
+  else
+    for (const auto& r : launch_ranges(b))
+      launch_p2g_col(in, b->N, b->envs_d, b->items_mat_d + r.first, r.count, b->grid[gi], b->flags[gi], b->errs, kc, b->box, r.mat, s);
 }
 
 void batched_grid(mpm_batch* b, int gi, int clear, int k_rel) {
@@ -253,34 +248,22 @@ void batched_grid(mpm_batch* b, int gi, int clear, int k_rel) {
 }
 
 void batched_g2p(mpm_batch* b, const float* in, float* out, int gi, int kc) {
-  const hipStream_t s = b->stream;
-  const int ni = (int)b->items_h.size();
   Span sp(b, KC_G2P);
-  if (b->var_g2p == 0) launch_g2p_direct(in, out, b->N, b->envs_d, b->items_d, ni, b->grid[gi], b->errs, kc, s);
-  else
-    for (const auto& r : launch_ranges(b))
-      launch_g2p_lds(in, out, b->N, b->envs_d, b->items_mat_d + r.first, r.count, b->grid[gi],
-                     b->errs, kc, b->grid_cap, b->box, r.mat, s);
+  for (const auto& r : launch_ranges(b))
+    launch_g2p(in, out, b->N, b->envs_d, b->items_mat_d + r.first, r.count, b->grid[gi], b->errs, kc, r.mat, b->stream);
 }
 
 // G2P of substep kc from grid gi_in fused with P2G of substep kc + 1 into grid gi_out
 void batched_g2p2g(mpm_batch* b, const float* in, float* out, int gi_in, int gi_out, int kc) {
-  const hipStream_t s = b->stream;
-  const int runs = b->min_run | (b->max_run << 16);
   Span sp(b, KC_G2P2G);
-  for (const auto& r : launch_ranges(b)) {
-    if (b->var_p2g == 3)
-      launch_g2p2g_pull(in, out, b->N, b->envs_d, b->items_mat_d + r.first, r.count, b->grid[gi_in],
-                        b->grid[gi_out], b->flags[gi_out], b->errs, kc, b->box, r.mat, s);
-    else
-      launch_g2p2g(in, out, b->N, b->envs_d, b->items_mat_d + r.first, r.count, b->grid[gi_in],
-                   b->grid[gi_out], b->flags[gi_out], b->errs, runs, kc, b->box, r.mat, s);
-  }
+  for (const auto& r : launch_ranges(b))
+    launch_g2p2g_col(in, out, b->N, b->envs_d, b->items_mat_d + r.first, r.count, b->grid[gi_in], b->grid[gi_out],
+                     b->flags[gi_out], b->errs, kc, b->box, r.mat, b->stream);
 }
 
-// the forward fusion pairs the G2P with the per-cell-run or the pull scatter
+// the forward fusion pairs the G2P with the column scatter
 bool fused(const mpm_batch* b) {
-  return b->mode != MPM_MODE_PLAIN && b->fuse && (b->var_p2g == 2 || b->var_p2g == 3);
+  return b->mode != MPM_MODE_PLAIN && b->fuse && b->var_p2g != 0;
 }
 
 void substep(mpm_batch* b, const float* in, float* out, int gi, int clear, int k_rel, int kc) {
@@ -306,17 +289,13 @@ void substep(mpm_batch* b, const float* in, float* out, int gi, int clear, int k
 // batched-mode pieces of a substep's adjoint
 void batched_g2p_adj(mpm_batch* b, const float* st, const float* st_next, const float* cot_in, int gi, int kc) {
   const hipStream_t s = b->stream;
-  const int ni = (int)b->items_h.size();
-  const int runs = b->min_run | (b->max_run << 16);
   float* g = b->grid[gi];
   Span sp(b, KC_G2P_ADJ);
-  if (b->var_g2p_adj == 0) launch_g2p_adjoint_direct(st, st_next, cot_in, b->part, b->N, b->envs_d, b->items_d, ni, g, b->gcot, b->pacc, kc, s);
-  for (const auto& r : launch_ranges(b)) {
-    const WorkItem* it = b->items_mat_d + r.first;
-    if (b->var_g2p_adj == 2) launch_g2p_adjoint_seg(st, st_next, cot_in, b->part, b->N, b->envs_d, it, r.count, g, b->gcot, b->pacc, runs, kc, b->grid_cap, b->box, r.mat, s);
-    else if (b->var_g2p_adj == 1) launch_g2p_adjoint_lds(st, st_next, cot_in, b->part, b->N, b->envs_d, it, r.count, g, b->gcot, b->pacc, kc, b->grid_cap, b->box, r.mat, s);
-    else if (b->var_g2p_adj == 3) launch_g2p_adjoint_pull(st, st_next, cot_in, b->part, b->N, b->envs_d, it, r.count, g, b->gcot, b->pacc, kc, b->grid_cap, b->box, r.mat, s);
-  }
+  if (b->var_g2p_adj == 0)
+    launch_g2p_adjoint_direct(st, st_next, cot_in, b->part, b->N, b->envs_d, b->items_d, (int)b->items_h.size(), g, b->gcot, b->pacc, kc, s);
+  else
+    for (const auto& r : launch_ranges(b))
+      launch_g2p_adjoint_col(st, st_next, cot_in, b->part, b->N, b->envs_d, b->items_mat_d + r.first, r.count, g, b->gcot, b->pacc, kc, b->box, r.mat, s);
 }
 
 void batched_grid_adj(mpm_batch* b, int gi, int k_rel) {
@@ -331,29 +310,18 @@ void batched_grid_adj(mpm_batch* b, int gi, int k_rel) {
 }
 
 void batched_p2g_adj(mpm_batch* b, const float* st, const float* cot_in, float* cot_out, int kc) {
-  const hipStream_t s = b->stream;
-  const int ni = (int)b->items_h.size();
   Span sp(b, KC_P2G_ADJ);
-  if (b->var_p2g_adj == 0) launch_p2g_adjoint_direct(st, b->part, cot_out, b->N, b->envs_d, b->items_d, ni, b->gcot, b->pacc, kc, cot_in, s);
-  else
-    for (const auto& r : launch_ranges(b))
-      launch_p2g_adjoint_lds(st, b->part, cot_out, b->N, b->envs_d, b->items_mat_d + r.first, r.count, b->gcot, b->pacc, kc, cot_in, b->grid_cap, b->box, r.mat, s);
+  for (const auto& r : launch_ranges(b))
+    launch_p2g_adjoint(st, b->part, cot_out, b->N, b->envs_d, b->items_mat_d + r.first, r.count, b->gcot, b->pacc, kc, cot_in, r.mat, b->stream);
 }
 
 // P2G adjoint of substep kc (state st) fused with the G2P adjoint of substep
 // kc - 1 (state st_prev, grid gi_prev); cot_end: the segment's incoming cotangent
 void batched_adj_pair(mpm_batch* b, const float* st_prev, const float* st, const float* cot_end, int gi_prev, int kc) {
-  const hipStream_t s = b->stream;
-  const int runs = b->min_run | (b->max_run << 16);
   Span sp(b, KC_ADJ_PAIR);
-  for (const auto& r : launch_ranges(b)) {
-    if (b->var_g2p_adj == 3)
-      launch_adj_pair_pull(st_prev, st, b->part, cot_end, b->N, b->envs_d, b->items_mat_d + r.first, r.count,
-                           b->grid[gi_prev], b->gcot, b->pacc, kc, b->box, r.mat, s);
-    else
-      launch_adj_pair(st_prev, st, b->part, cot_end, b->N, b->envs_d, b->items_mat_d + r.first,
-                      r.count, b->grid[gi_prev], b->gcot, b->pacc, runs, kc, b->box, r.mat, s);
-  }
+  for (const auto& r : launch_ranges(b))
+    launch_adj_pair_col(st_prev, st, b->part, cot_end, b->N, b->envs_d, b->items_mat_d + r.first, r.count,
+                        b->grid[gi_prev], b->gcot, b->pacc, kc, b->box, r.mat, b->stream);
 }
 
 bool fused_adj(const mpm_batch* b) { return b->mode != MPM_MODE_PLAIN && b->fuse_adj; }
@@ -651,7 +619,7 @@ void* batch_stream(const mpm_batch* b) { return (void*)b->stream; }
 namespace {
 
 struct TuneChoice {
-  int p2g, g2p, g2p_adj, p2g_adj, min_run, grid_cap, max_run, box, specialize, fuse, fuse_adj, xcd, grid_list;
+  int p2g, g2p_adj, box, specialize, fuse, fuse_adj, xcd, grid_list;
 };
 
 // shape signature -> choice, shared by batches of the same shape in the process
@@ -668,10 +636,7 @@ std::string shape_signature(const mpm_batch* b) {
 }
 
 void apply_choice(mpm_batch* b, const TuneChoice& c) {
-  b->var_p2g = c.p2g; b->var_g2p = c.g2p; b->var_g2p_adj = c.g2p_adj; b->var_p2g_adj = c.p2g_adj;
-  b->min_run = c.min_run;
-  b->grid_cap = c.grid_cap;
-  b->max_run = c.max_run;
+  b->var_p2g = c.p2g; b->var_g2p_adj = c.g2p_adj;
   b->box = c.box;
   b->specialize = c.specialize;
   b->fuse = c.fuse;
@@ -1424,7 +1389,7 @@ int mpm_autotune(mpm_batch* b, int32_t budget_ms) {
     return std::chrono::duration<double, std::milli>(std::chrono::steady_clock::now() - t_start).count() > budget_ms;
   };
   // reference results: one thread per particle, global atomics
-  TuneChoice best{0, 0, 0, 0, b->min_run, 0, b->max_run, 0, 1, 0, 0, 0, 0};
+  TuneChoice best{0, 0, 0, 1, 0, 0, 0, 0};
   apply_choice(b, best);
   int rc = run_fwd(ref);
   if (!rc) rc = run_bwd(gref);
@@ -1442,25 +1407,18 @@ int mpm_autotune(mpm_batch* b, int32_t budget_ms) {
     ms = f;
     return MPM_OK;
   };
-  // one candidate: a field of TuneChoice, its value, optional min_run, timed with the backward
-  struct Cand { int* slot; int value; int min_run; bool bwd; };
+  best = {2, 2, 0, 1, 1, 1, 0, 0};   // the defaults, from which one option after another is tried
+  // one candidate: a field of TuneChoice and its value; timed with the backward or forward only
+  struct Cand { int* slot; int value; bool bwd; };
   std::vector<std::vector<Cand>> groups = {
-      {{&best.p2g, 0, 0, false}, {&best.p2g, 1, 0, false}, {&best.p2g, 2, 2, false}, {&best.p2g, 2, 3, false},
-       {&best.p2g, 2, 4, false}, {&best.p2g, 2, 8, false}, {&best.p2g, 3, 0, false}},
-      {{&best.g2p, 0, 0, false}, {&best.g2p, 1, 0, false}},
-      {{&best.g2p_adj, 0, 0, true}, {&best.g2p_adj, 1, 0, true}, {&best.g2p_adj, 2, 0, true},
-       {&best.g2p_adj, 3, 0, true}},
-      {{&best.p2g_adj, 0, 0, true}, {&best.p2g_adj, 1, 0, true}},
-      {{&best.box, 0, 0, true}, {&best.box, 1, 0, true}},
-      {{&best.specialize, 1, 0, true}, {&best.specialize, 0, 0, true}},
-      {{&best.fuse, 0, 0, true}, {&best.fuse, 1, 0, true}},
-      {{&best.fuse_adj, 0, 0, true}, {&best.fuse_adj, 1, 0, true}},
-      {{&best.xcd, 0, 0, true}, {&best.xcd, 1, 0, true}},
-      {{&best.grid_list, 0, 0, true}, {&best.grid_list, 1, 0, true}, {&best.grid_list, 2, 0, true}},
-      {{&best.grid_cap, 0, 0, true}, {&best.grid_cap, 512, 0, true}, {&best.grid_cap, 1024, 0, true},
-       {&best.grid_cap, 2048, 0, true}},
-      {{&best.max_run, 4, 0, true}, {&best.max_run, 8, 0, true}, {&best.max_run, 16, 0, true},
-       {&best.max_run, 256, 0, true}},
+      {{&best.p2g, 2, false}, {&best.p2g, 0, false}},
+      {{&best.g2p_adj, 2, true}, {&best.g2p_adj, 0, true}},
+      {{&best.box, 0, true}, {&best.box, 1, true}},
+      {{&best.specialize, 1, true}, {&best.specialize, 0, true}},
+      {{&best.fuse, 1, true}, {&best.fuse, 0, true}},
+      {{&best.fuse_adj, 1, true}, {&best.fuse_adj, 0, true}},
+      {{&best.xcd, 0, true}, {&best.xcd, 1, true}},
+      {{&best.grid_list, 0, true}, {&best.grid_list, 1, true}, {&best.grid_list, 2, true}},
   };
   for (auto& grp : groups) {
     if (rc) break;
@@ -1471,7 +1429,6 @@ int mpm_autotune(mpm_batch* b, int32_t budget_ms) {
       if (over_budget() && best_ms < 1e30) break;
       TuneChoice trial = keep;
       *(&trial.p2g + (c.slot - &best.p2g)) = c.value;
-      if (c.min_run > 0) trial.min_run = c.min_run;
       apply_choice(b, trial);
       double ms = 0.0, err = 0.0;
       rc = time_it(c.bwd, ms);
