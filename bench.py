@@ -79,7 +79,7 @@ def kernel_instance(symbol: str, tuned: dict, envs) -> str:
         return symbol
     mats = sorted({e.material for e in envs})
     mat = mats[0] if tuned["SPECIALIZE"] and len(mats) == 1 else -1
-    return f"{symbol}<{384 if tuned['BOX'] else 1024}, {mat}>" if symbol.endswith("_col") else f"{symbol}<{mat}>"
+    return f"{symbol}<{640 if tuned['BOX'] else 1024}, {mat}>" if symbol.endswith("_col") else f"{symbol}<{mat}>"
 
 
 def measured_traffic(workload: str, symbol: str):

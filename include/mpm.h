@@ -322,7 +322,7 @@ int mpm_backward(mpm_batch* b, const float* gx, const float* gv, const float* gC
 #define MPM_OPT_GRID_CAP 7     /*   1 .. 256 (default 8): accepted and read back; no kernel depends on them */
 #define MPM_OPT_MAX_RUN 8
 #define MPM_OPT_BOX 9          /* LDS budget of the column sums: 0 = 1024 grid nodes per block and pass (default),
-                                  1 = 384 (less LDS, more blocks per CU; a block with more nodes takes more passes) */
+                                  1 = 640 (less LDS, more blocks per CU; a block with more nodes takes more passes) */
 #define MPM_OPT_FUSE 11        /* 1 (default): within a segment, G2P of substep k and the P2G of substep k + 1 run as
                                   one kernel (the new state is scattered from registers); needs MPM_OPT_P2G != 0,
                                   otherwise ignored. 0: two kernels */

@@ -79,7 +79,7 @@ void launch_p2g_adjoint_direct(const float* st, const float* part, float* cot_ou
 
 // Particle kernels of the batched mode (mpm_kernels_col.hip). Each launch covers
 // work items of one material `mat`, compiled for it (-1: any, read at run
-// time); `box` picks the scatter's LDS box budget (0: 1024 nodes, 1: 384).
+// time); `box` picks the scatter's LDS box budget (0: 1024 nodes, 1: 640).
 void launch_p2g_col(const float* st, int64_t N, const EnvDev* envs, const WorkItem* items, int n_items, float* grid,
                     uint32_t* flags, int32_t* errs, int k_call, int box, int mat, hipStream_t s);
 void launch_g2p(const float* st, float* out, int64_t N, const EnvDev* envs, const WorkItem* items, int n_items,

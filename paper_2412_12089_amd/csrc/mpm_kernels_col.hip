@@ -33,17 +33,40 @@ constexpr int kBins = 8;           // task lengths told apart
 // Box budgets in nodes (a block with more takes several passes over slabs of z)
 // and room for base cells (a block with more adds to the grid directly). The
 // larger pair leaves four blocks per CU (LDS) and holds a box of 28 z nodes
-// across a whole tile row; the small one holds the few cells a block of many
-// particles per cell covers, and leaves six.
+// across a whole tile row. The smaller one with its 96 VGPRs leaves five
+// (32,000 bytes of LDS is the most for that): the scatter's barriers and
+// LDS chains want the fifth where the boxes fit. G2P2G, 2 M elastic particles
+// (256 envs, 6 per cell) 65.8 -> 60.9 us, 1 M von Mises (4 envs, 8 per cell) 53 ->
+// 46; where they do not, at 1.3 particles per cell, the second pass costs
+// more: 8 M water particles 289 -> 298. (384 nodes with six blocks lost to
+// one of the two at each of these.) The autotuner measures both.
 constexpr int kBoxLarge = 1024;
-constexpr int kBoxSmall = 384;
+constexpr int kBoxSmall = 640;
 template <int BOXN>
-constexpr int col_cells() { return BOXN == kBoxLarge ? 1024 : 512; }
+constexpr int col_cells() { return BOXN; }
+template <int BOXN>
+constexpr int waves_per_simd() { return BOXN == kBoxLarge ? 4 : 5; }
 
-// whole-wavefront reductions (DPP, device library)
-extern "C" __device__ __attribute__((const)) int __ockl_wfred_min_i32(int);
-extern "C" __device__ __attribute__((const)) int __ockl_wfred_max_i32(int);
+// whole-wavefront sum (DPP, device library)
 extern "C" __device__ __attribute__((const)) float __ockl_wfred_add_f32(float);
+
+// smallest of each 16-bit half over the wavefront
+typedef short short2v __attribute__((ext_vector_type(2)));
+template <int CTRL, int ROWS>
+MD int pk_min_dpp(int x) {
+  const int y = __builtin_amdgcn_update_dpp(x, x, CTRL, ROWS, 0xf, false);
+  const short2v m = __builtin_elementwise_min(__builtin_bit_cast(short2v, x), __builtin_bit_cast(short2v, y));
+  return __builtin_bit_cast(int, m);
+}
+MD int wave_pk_min(int x) {
+  x = pk_min_dpp<0xB1, 0xf>(x);    // quad_perm [1, 0, 3, 2]
+  x = pk_min_dpp<0x4E, 0xf>(x);    // quad_perm [2, 3, 0, 1]
+  x = pk_min_dpp<0x124, 0xf>(x);   // row_ror 4 and 8: all 16 lanes of a row
+  x = pk_min_dpp<0x128, 0xf>(x);
+  x = pk_min_dpp<0x142, 0xa>(x);   // row_bcast 15: rows 1 and 3 take in rows 0 and 2
+  x = pk_min_dpp<0x143, 0xc>(x);   // row_bcast 31: rows 2 and 3 take in row 1
+  return __builtin_amdgcn_readlane(x, 63);
+}
 
 // the block's runs (distinct tile rows): boxes of nodes, base cells
 // and (base column, z node) tasks, each concatenated over the runs. A run lies in one tile row, so it has at most 4 x
@@ -51,6 +74,7 @@ extern "C" __device__ __attribute__((const)) float __ockl_wfred_add_f32(float);
 struct Runs {
   int last[4], wsum[4];               // per wave: its last particle's tile row; row changes in it
   int rows[4][kWaveRows];             // per wave: the tile row after each change
+  int cols[kMaxRuns], zmin[kMaxRuns], zmax[kMaxRuns];   // base columns in use (x bits 0-3, y 4-7), base z bounds
   int lo[kMaxRuns][3], hi[kMaxRuns][3];   // node bounds (inclusive)
   int ext[kMaxRuns][3];
   int node[kMaxRuns + 1], cell[kMaxRuns + 1], task[kMaxRuns + 1];   // first of each run, then the total
@@ -76,22 +100,36 @@ struct ColShared {
 // the product) move it by less than (a + 1/2) / d * 2^-23 < 1/(2d)
 MD int small_div(int a, float inv_d) { return (int)(((float)a + 0.5f) * inv_d); }
 
-MD void load_x3(const float* __restrict__ st, int64_t N, int64_t p, float x[3]) {
-  x[0] = st[p]; x[1] = st[N + p]; x[2] = st[2 * N + p];
+// State and cotangent rows of a block's particles: `base` points at the block's
+// first particle (uniform over the block), t is the thread's particle in the
+// block, so that each access is one scalar base and the same 32-bit lane offset.
+MD void load_x3(const float* __restrict__ base, int64_t N, uint32_t t, float x[3]) {
+  x[0] = base[t]; x[1] = (base + N)[t]; x[2] = (base + 2 * N)[t];
 }
-MD M3 ld_m3(const float* __restrict__ st, int64_t N, int64_t p, int c0) {
+MD M3 ld_m3(const float* __restrict__ base, int64_t N, uint32_t t, int c0) {
   M3 m;
 #pragma unroll
   for (int i = 0; i < 3; ++i)
 #pragma unroll
-    for (int j = 0; j < 3; ++j) m.m[i][j] = st[(c0 + 3 * i + j) * N + p];
+    for (int j = 0; j < 3; ++j) m.m[i][j] = (base + (c0 + 3 * i + j) * N)[t];
   return m;
 }
-MD void st_m3(float* __restrict__ st, int64_t N, int64_t p, int c0, const M3& m) {
+MD void st_m3(float* __restrict__ base, int64_t N, uint32_t t, int c0, const M3& m) {
 #pragma unroll
   for (int i = 0; i < 3; ++i)
 #pragma unroll
-    for (int j = 0; j < 3; ++j) st[(c0 + 3 * i + j) * N + p] = m.m[i][j];
+    for (int j = 0; j < 3; ++j) (base + (c0 + 3 * i + j) * N)[t] = m.m[i][j];
+}
+MD void ld_v3(const float* __restrict__ base, int64_t N, uint32_t t, int c0, float v[3]) {
+#pragma unroll
+  for (int a = 0; a < 3; ++a) v[a] = (base + (c0 + a) * N)[t];
+}
+MD void st_v3(float* __restrict__ base, int64_t N, uint32_t t, int c0, const float v[3]) {
+#pragma unroll
+  for (int a = 0; a < 3; ++a) (base + (c0 + a) * N)[t] = v[a];
+}
+MD void copy_rows(const float* __restrict__ src, float* __restrict__ dst, int64_t N, uint32_t t) {
+  for (int c = 0; c < 24; ++c) (dst + c * N)[t] = (src + c * N)[t];
 }
 
 // a[i] for a runtime i in {0,1,2} without indexing a register array
@@ -141,7 +179,7 @@ MD bool col_index(const EnvDev& e, const int b[3], bool valid, ColShared<BOXN>& 
   Runs& R = S.r;
   for (int i = t; i <= col_cells<BOXN>(); i += kItem) S.start[i] = 0;
   if (t == 0) R.occupied = 0;
-  if (t < kMaxRuns * 3) { R.lo[t / 3][t % 3] = 0x3fffffff; R.hi[t / 3][t % 3] = -0x3fffffff; }
+  if (t < kMaxRuns) { R.cols[t] = 0; R.zmin[t] = 0x7fff; R.zmax[t] = 0; }
   const int row = valid ? (b[0] >> 2) * e.T + (b[1] >> 2) : -1;
   int prev = __shfl_up(row, 1);
   if (lane == 63) R.last[wave] = row;
@@ -171,27 +209,40 @@ MD bool col_index(const EnvDev& e, const int b[3], bool valid, ColShared<BOXN>& 
     ++nr;
   }
   if (__ballot(over) != 0ull || rest != 0ull) nr = 0;   // too many: the caller adds to the grid directly
-  // bounds of each run's stencils: a reduction in registers per wave, then one integer atomic per wave
+  // bounds of each run: which of its tile row's four columns in x and in y are in use (ballots), and base z
+  // (one packed reduction); then integer atomics per wave
   for (int k = 0; k < nr; ++k) {
     const bool mine = run == k;
-    if (__ballot(mine) == 0ull) continue;
+    const uint64_t of_k = __ballot(mine);
+    if (of_k == 0ull) continue;
+    int cols = 0;
 #pragma unroll
-    for (int a = 0; a < 3; ++a) {
-      const int mn = __ockl_wfred_min_i32(mine ? b[a] : 0x3fffffff);
-      const int mx = __ockl_wfred_max_i32(mine ? b[a] + 2 : -0x3fffffff);
-      if (lane == 0) { atomicMin(&R.lo[k][a], mn); atomicMax(&R.hi[k][a], mx); }
+    for (int j = 0; j < 4; ++j) {
+      cols |= __ballot(mine && (b[0] & 3) == j) != 0ull ? 1 << j : 0;
+      cols |= __ballot(mine && (b[1] & 3) == j) != 0ull ? 16 << j : 0;
+    }
+    const int z = wave_pk_min(mine ? (b[2] & 0xffff) | (-b[2] << 16) : 0x7fff7fff);
+    const int first_of_k = __ffsll((unsigned long long)of_k) - 1;
+    const int tx = __builtin_amdgcn_readlane(b[0], first_of_k) & ~3, ty = __builtin_amdgcn_readlane(b[1], first_of_k) & ~3;
+    if (lane == 0) {
+      atomicOr(&R.cols[k], cols);
+      atomicMin(&R.zmin[k], (int)(short)(z & 0xffff));
+      atomicMax(&R.zmax[k], -(z >> 16));
+      R.lo[k][0] = tx;   // the same value from every wave: the row's first node; the tight bound follows
+      R.lo[k][1] = ty;
     }
   }
   __syncthreads();
   // every thread derives the tables; thread 0 keeps them for the scatter
   int node = 0, cell = 0, task = 0, cid = 0;
   for (int k = 0; k < nr; ++k) {
-    const int lo[3] = {R.lo[k][0], R.lo[k][1], R.lo[k][2]};
-    const int ext[3] = {R.hi[k][0] - lo[0] + 1, R.hi[k][1] - lo[1] + 1, R.hi[k][2] - lo[2] + 1};
+    const int cols = R.cols[k], cx = cols & 15, cy = (cols >> 4) & 15;
+    const int lo[3] = {R.lo[k][0] + __ffs(cx) - 1, R.lo[k][1] + __ffs(cy) - 1, R.zmin[k]};
+    const int ext[3] = {32 - __clz(cx) - __ffs(cx) + 3, 32 - __clz(cy) - __ffs(cy) + 3, R.zmax[k] - lo[2] + 3};
     if (run == k) cid = cell + ((b[0] - lo[0]) * (ext[1] - 2) + (b[1] - lo[1])) * (ext[2] - 2) + (b[2] - lo[2]);
     if (t == 0) {
       R.node[k] = node; R.cell[k] = cell; R.task[k] = task;
-      for (int a = 0; a < 3; ++a) R.ext[k][a] = ext[a];
+      for (int a = 0; a < 3; ++a) { R.ext[k][a] = ext[a]; R.hi[k][a] = lo[a] + ext[a] - 1; }
       R.inv_z[k] = 1.f / (float)ext[2];
       R.inv_cy[k] = 1.f / (float)(ext[1] - 2);
     }
@@ -207,6 +258,7 @@ MD bool col_index(const EnvDev& e, const int b[3], bool valid, ColShared<BOXN>& 
   const uint64_t firsts = __ballot(valid && rank == 0);
   if (lane == 0) atomicAdd(&R.occupied, (int)__popcll(firsts));
   __syncthreads();
+  if (t < kMaxRuns * 3 && t / 3 < nr) R.lo[t / 3][t % 3] = R.hi[t / 3][t % 3] - R.ext[t / 3][t % 3] + 1;   // the tight bounds
   // block-wide inclusive prefix sum of start[0, cell]
   const int n = cell + 1, per = (n + kItem - 1) / kItem;
   const int i0 = min(t * per, n), i1 = min(i0 + per, n);
@@ -463,53 +515,65 @@ MD void direct_scatter(const EnvDev& e, const Stencil& sc, const float g[3], con
 // ----------------------------------------------------------------------------
 // pieces of the substep for one particle
 // ----------------------------------------------------------------------------
-// G2P gather: v = sum W v_i, C = 4 n^2 sum W v_i d^T at position x
+// G2P gather: v = sum W v_i, C = 4 n^2 sum W v_i d^T at position x. The sums are
+// taken axis by axis (z, then y, then x), which weighs a partial sum once
+// instead of each node.
 MD void gather_v(const EnvDev& e, const float* __restrict__ grid, const float x[3], float vn[3], M3& Cn) {
   const Stencil sc = make_stencil(x, e.n, e.fn);
   const StencilAddr sa = stencil_addr(e, sc.b);
   const float* genv = grid + (int64_t)e.tile_off * 512 + G1;
   Cn = m3_zero();
   vn[0] = vn[1] = vn[2] = 0.f;
-  float wdz[3];
-  for (int o = 0; o < 3; ++o) wdz[o] = sc.w[2][o] * (((float)o - sc.f[2]) * e.dx);
+  float wdz[3], wdy[3];
+  for (int o = 0; o < 3; ++o) {
+    wdz[o] = sc.w[2][o] * ((float)o - sc.f[2]);
+    wdy[o] = sc.w[1][o] * ((float)o - sc.f[1]);
+  }
 #pragma unroll 1
   for (int ox = 0; ox < 3; ++ox) {
     const uint32_t ax = ox == 0 ? sa.x[0] : (ox == 1 ? sa.x[1] : sa.x[2]);
-    const float wx = sel3(sc.w[0], ox), d0 = ((float)ox - sc.f[0]) * e.dx;
+    float sy[3] = {0.f, 0.f, 0.f}, syd[3] = {0.f, 0.f, 0.f}, syz[3] = {0.f, 0.f, 0.f};   // sums of v, v d_y, v d_z
 #pragma unroll
     for (int oy = 0; oy < 3; ++oy) {
-      // a z-column shares d_x and d_y: sum W v_i and W v_i d_z over it, then add the column into v and C
-      const float wxy = wx * sc.w[1][oy], d1 = ((float)oy - sc.f[1]) * e.dx;
       float col[3] = {0.f, 0.f, 0.f}, colz[3] = {0.f, 0.f, 0.f};
 #pragma unroll
       for (int oz = 0; oz < 3; ++oz) {
         const float4 v4 = ld4(genv + (ax + sa.y[oy] + sa.z[oz]));
         const float vi[3] = {v4.x, v4.y, v4.z};
-        const float W = wxy * sc.w[2][oz], Wd = wxy * wdz[oz];
 #pragma unroll
         for (int a = 0; a < 3; ++a) {
-          col[a] = fmaf(W, vi[a], col[a]);
-          colz[a] = fmaf(Wd, vi[a], colz[a]);
+          col[a] = fmaf(sc.w[2][oz], vi[a], col[a]);
+          colz[a] = fmaf(wdz[oz], vi[a], colz[a]);
         }
       }
 #pragma unroll
       for (int a = 0; a < 3; ++a) {
-        vn[a] += col[a];
-        Cn.m[a][0] = fmaf(col[a], d0, Cn.m[a][0]);
-        Cn.m[a][1] = fmaf(col[a], d1, Cn.m[a][1]);
-        Cn.m[a][2] += colz[a];
+        sy[a] = fmaf(sc.w[1][oy], col[a], sy[a]);
+        syd[a] = fmaf(wdy[oy], col[a], syd[a]);
+        syz[a] = fmaf(sc.w[1][oy], colz[a], syz[a]);
       }
     }
+    float wx, dwx;
+    spline_piece(ox, sc.f[0], wx, dwx);
+    const float wdx = wx * ((float)ox - sc.f[0]);
+#pragma unroll
+    for (int a = 0; a < 3; ++a) {
+      vn[a] = fmaf(wx, sy[a], vn[a]);
+      Cn.m[a][0] = fmaf(wdx, sy[a], Cn.m[a][0]);
+      Cn.m[a][1] = fmaf(wx, syd[a], Cn.m[a][1]);
+      Cn.m[a][2] = fmaf(wx, syz[a], Cn.m[a][2]);
+    }
   }
-  Cn = m3_scale(Cn, 4.f * e.fn * e.fn);
+  Cn = m3_scale(Cn, 4.f * e.fn);   // 4 n^2 dx
 }
 
 // writes a particle's new state and reports a non-finite one
-MD void store_new_state(float* __restrict__ out, int64_t N, int64_t p, const float xn[3], const float vn[3],
+MD void store_new_state(float* __restrict__ out, int64_t N, uint32_t t, const float xn[3], const float vn[3],
                         const M3& Cn, const M3& Hn, int32_t* err) {
-  for (int a = 0; a < 3; ++a) { out[a * N + p] = xn[a]; out[(3 + a) * N + p] = vn[a]; }
-  st_m3(out, N, p, 6, Cn);
-  st_m3(out, N, p, 15, Hn);
+  st_v3(out, N, t, 0, xn);
+  st_v3(out, N, t, 3, vn);
+  st_m3(out, N, t, 6, Cn);
+  st_m3(out, N, t, 15, Hn);
   bool fin = true;
   for (int a = 0; a < 3; ++a) fin = fin && isfinite(xn[a]) && isfinite(vn[a]);
   for (int i = 0; i < 3; ++i) for (int j = 0; j < 3; ++j) fin = fin && isfinite(Hn.m[i][j]);
@@ -548,43 +612,44 @@ MD void p2g_col_body(const EnvDev& e, int mat, bool valid, const float x[3], Loa
 
 // P2G adjoint of one particle: gathers (mbar, Pbar), adds the G2P part
 // (x rows 0-2 and F rows 3-11 of part) and returns the state cotangent.
-// eig: 12 floats per thread that keep the eigen-decomposition of B across the
-// stencil loop (only A and v stay live through it).
+// st, part: the block's first particle's rows. eig: 12 floats per thread that
+// keep the eigen-decomposition of B across the stencil loop (only A and v stay
+// live through it). The node sums are taken per (x, y) column; with
+// gw = m_p mbar + Pbar (m_p v + A d) per node, a column needs sums of w_z gw and
+// w_z' gw for the position, of w_z mbar, w_z Pbar and w_z d_z Pbar for the rest.
 template <int MAT>
 MD void p2g_adjoint_particle(const EnvDev& e, int mat, const float* __restrict__ st, const float* part, int64_t N,
-                             int64_t p, const float* gcot, float (*eig)[kItem], float pb[PB_COUNT], float cx[3],
+                             uint32_t t, const float* gcot, float (*eig)[kItem], float pb[PB_COUNT], float cx[3],
                              float cv[3], M3& cC, M3& cF) {
   constexpr bool kEig = MAT == MAT_COROTATED || MAT == MAT_VONMISES || MAT < 0;
   const bool use_eig = kEig && (mat == MAT_COROTATED || mat == MAT_VONMISES);
-  const int t = threadIdx.x;
-  float x[3];
-  load_x3(st, N, p, x);
+  float x[3], v[3];
+  load_x3(st, N, t, x);
+  ld_v3(st, N, t, 3, v);
   const Stencil sc = make_stencil(x, e.n, e.fn);
   const StencilAddr sa = stencil_addr(e, sc.b);
   const float* genv = gcot + (int64_t)e.tile_off * 512 + G1;
   const float kf = -e.dt * e.vp * 4.f * e.fn * e.fn;
-  const float v[3] = {st[3 * N + p], st[4 * N + p], st[5 * N + p]};
-  M3 A;
+  M3 A;   // times dx: offsets d in grid units below
   {
-    const M3 Cm = ld_m3(st, N, p, 6);
-    const M3 H = ld_m3(st, N, p, 15);
+    const M3 Cm = ld_m3(st, N, t, 6);
+    const M3 H = ld_m3(st, N, t, 15);
     const StressPrep spr = stress_prep(e, H, mat);
-    A = m3_axpy(m3_scale(Cm, e.mp), kf, stress_from(e, spr, mat));
+    A = m3_scale(m3_axpy(m3_scale(Cm, e.mp), kf, stress_from(e, spr, mat)), e.dx);
     if (use_eig)
       for (int i = 0; i < 3; ++i) {
         eig[9 + i][t] = spr.l[i];
         for (int j = 0; j < 3; ++j) eig[3 * i + j][t] = spr.U.m[i][j];
       }
   }
-  float xb[3] = {part[p], part[N + p], part[2 * N + p]};
+  float gx[3] = {0.f, 0.f, 0.f};   // sum of grad W gw, grid units
   float sP[3] = {0.f, 0.f, 0.f};   // sum of W Pbar
   float sm = 0.f;                  // sum of W mbar
-  M3 Ab = m3_zero();               // sum of W Pbar d^T
+  M3 Ab = m3_zero();               // sum of W Pbar d^T, grid units
 #pragma unroll 1
   for (int ox = 0; ox < 3; ++ox)
 #pragma unroll 1
     for (int oy = 0; oy < 3; ++oy) {
-      // the column's three z-nodes are loaded together, then summed
       const uint32_t axy = (ox == 0 ? sa.x[0] : (ox == 1 ? sa.x[1] : sa.x[2])) +
                            (oy == 0 ? sa.y[0] : (oy == 1 ? sa.y[1] : sa.y[2]));
       float4 mP[3];
@@ -593,37 +658,41 @@ MD void p2g_adjoint_particle(const EnvDev& e, int mat, const float* __restrict__
       float wx, wy, dwx, dwy;
       spline_piece(ox, sc.f[0], wx, dwx);
       spline_piece(oy, sc.f[1], wy, dwy);
-      const float wxy = wx * wy, gxw = e.fn * dwx * wy, gyw = e.fn * wx * dwy;
-      const float d0 = ((float)ox - sc.f[0]) * e.dx, d1 = ((float)oy - sc.f[1]) * e.dx;
-      // column invariant m_p v + A d at d_z = 0; column sums of W Pbar and W Pbar d_z
-      float uc[3], cP[3] = {0.f, 0.f, 0.f}, cPz[3] = {0.f, 0.f, 0.f};
+      const float d0 = (float)ox - sc.f[0], d1 = (float)oy - sc.f[1], wxy = wx * wy;
+      float uc[3], cP[3] = {0.f, 0.f, 0.f}, cPz[3] = {0.f, 0.f, 0.f}, cm = 0.f, s0 = 0.f, s1 = 0.f;
       for (int a = 0; a < 3; ++a) uc[a] = fmaf(A.m[a][0], d0, fmaf(A.m[a][1], d1, e.mp * v[a]));
 #pragma unroll
       for (int oz = 0; oz < 3; ++oz) {
-        const float wz = sc.w[2][oz], dz = ((float)oz - sc.f[2]) * e.dx;
-        const float W = wxy * wz, Wd = W * dz;
-        const float gW[3] = {gxw * wz, gyw * wz, wxy * e.fn * sc.dw[2][oz]};
+        const float wz = sc.w[2][oz], dz = (float)oz - sc.f[2], wzd = wz * dz;
         const float Pb[3] = {mP[oz].y, mP[oz].z, mP[oz].w};
         float gw = e.mp * mP[oz].x;
         for (int a = 0; a < 3; ++a) gw = fmaf(Pb[a], fmaf(A.m[a][2], dz, uc[a]), gw);
-        sm = fmaf(W, mP[oz].x, sm);
+        s0 = fmaf(wz, gw, s0);
+        s1 = fmaf(sc.dw[2][oz], gw, s1);
+        cm = fmaf(wz, mP[oz].x, cm);
         for (int a = 0; a < 3; ++a) {
-          cP[a] = fmaf(W, Pb[a], cP[a]);
-          cPz[a] = fmaf(Wd, Pb[a], cPz[a]);
-          xb[a] = fmaf(gW[a], gw, xb[a]);
+          cP[a] = fmaf(wz, Pb[a], cP[a]);
+          cPz[a] = fmaf(wzd, Pb[a], cPz[a]);
         }
       }
+      gx[0] = fmaf(dwx * wy, s0, gx[0]);
+      gx[1] = fmaf(wx * dwy, s0, gx[1]);
+      gx[2] = fmaf(wxy, s1, gx[2]);
+      sm = fmaf(wxy, cm, sm);
+      const float w0 = wxy * d0, w1 = wxy * d1;
       for (int a = 0; a < 3; ++a) {
-        sP[a] += cP[a];
-        Ab.m[a][0] = fmaf(cP[a], d0, Ab.m[a][0]);
-        Ab.m[a][1] = fmaf(cP[a], d1, Ab.m[a][1]);
-        Ab.m[a][2] += cPz[a];
+        sP[a] = fmaf(wxy, cP[a], sP[a]);
+        Ab.m[a][0] = fmaf(w0, cP[a], Ab.m[a][0]);
+        Ab.m[a][1] = fmaf(w1, cP[a], Ab.m[a][1]);
+        Ab.m[a][2] = fmaf(wxy, cPz[a], Ab.m[a][2]);
       }
     }
-  // the stencil sum of -W A^T Pbar is -A^T sP
-  for (int a = 0; a < 3; ++a) xb[a] -= A.m[0][a] * sP[0] + A.m[1][a] * sP[1] + A.m[2][a] * sP[2];
-  const M3 Cm = ld_m3(st, N, p, 6);
-  const M3 H = ld_m3(st, N, p, 15);
+  // x: grad W = n dw, and the stencil sum of -W A^T Pbar is -A^T sP (A / dx = n A here)
+  for (int a = 0; a < 3; ++a)
+    cx[a] = fmaf(e.fn, gx[a] - (A.m[0][a] * sP[0] + A.m[1][a] * sP[1] + A.m[2][a] * sP[2]), (part + a * N)[t]);
+  Ab = m3_scale(Ab, e.dx);
+  const M3 Cm = ld_m3(st, N, t, 6);
+  const M3 H = ld_m3(st, N, t, 15);
   StressPrep spr;
   if (use_eig) {
     M3 U;
@@ -640,11 +709,11 @@ MD void p2g_adjoint_particle(const EnvDev& e, int mat, const float* __restrict__
   // m_p enters m_i (weight W) and P_i through m_p (v + C d): the C d part
   // summed over the nodes is <C, sum W Pbar d^T>
   const float mpb = sm + v[0] * sP[0] + v[1] * sP[1] + v[2] * sP[2] + m3_ddot(Cm, Ab);
-  for (int a = 0; a < 3; ++a) { cx[a] = xb[a]; cv[a] = e.mp * sP[a]; }
+  for (int a = 0; a < 3; ++a) cv[a] = e.mp * sP[a];
   cC = m3_scale(Ab, e.mp);
   pb[PB_VP] += (-e.dt * 4.f * e.fn * e.fn) * m3_ddot(Ab, tau);
   pb[PB_MP] += mpb;
-  cF = ld_m3(part, N, p, 3);
+  cF = ld_m3(part, N, t, 3);
   stress_vjp_from(e, H, spr, m3_scale(Ab, kf), cF, pb, mat);
 }
 
@@ -652,74 +721,84 @@ MD void p2g_adjoint_particle(const EnvDev& e, int mat, const float* __restrict__
 // (cx, cv, cC, cF) of the substep's output state -> the particle's partial
 // cotangent (part rows 0-2: x, 3-11: F), the node-velocity cotangents added to
 // group 0 of gcot. st: the substep's input state, st_next: its output (the
-// tape's C' is the forward's own value).
+// tape's C' is the forward's own value); both and part: the block's first
+// particle's rows.
 template <int BOXN>
-MD void g2p_adjoint_body(const EnvDev& e, int mat, bool valid, int64_t p, const float* __restrict__ st,
+MD void g2p_adjoint_body(const EnvDev& e, int mat, bool valid, uint32_t t, const float* __restrict__ st,
                          const float* __restrict__ st_next, int64_t N, const float cx[3], const float cv[3],
                          const M3& cC, const M3& cF, float* part, const float* __restrict__ grid, float* gcot,
                          float pb[PB_COUNT], ColShared<BOXN>& S) {
   float x[3];
-  load_x3(st, N, p, x);
+  load_x3(st, N, t, x);
   const Stencil sc = make_stencil(x, e.n, e.fn);
   int pos = 0;
   const bool fits = col_index<BOXN>(e, sc.b, valid, S, pos);
   if (valid) {
-    const float D4 = 4.f * e.fn * e.fn;
-    float vb[3], Ad[3][3];
-    for (int a = 0; a < 3; ++a) vb[a] = cv[a] + e.dt * cx[a];
-    M3 Cb;
+    float vb[3];
+    for (int a = 0; a < 3; ++a) vb[a] = fmaf(e.dt, cx[a], cv[a]);
+    float Ad[3][3];   // 4 n^2 dx Cbar
     {
-      const M3 H = ld_m3(st, N, p, 15);
-      const M3 Cn = ld_m3(st_next, N, p, 6);
+      const M3 H = ld_m3(st, N, t, 15);
+      const M3 Cn = ld_m3(st_next, N, t, 6);
       const M3 Ftrb = project_vjp(e, trial_h(e, Cn, H), cF, pb, mat);
-      Cb = m3_axpy(cC, e.dt, m3_mul_abt(Ftrb, f_of(H)));
-      st_m3(part, N, p, 3, m3_mul_atb(m3_axpy(m3_eye(), e.dt, Cn), Ftrb));
+      const M3 Cb = m3_axpy(cC, e.dt, m3_mul_abt(Ftrb, f_of(H)));
+      st_m3(part, N, t, 3, m3_mul_atb(m3_axpy(m3_eye(), e.dt, Cn), Ftrb));
+      for (int a = 0; a < 3; ++a)
+        for (int c = 0; c < 3; ++c) Ad[a][c] = 4.f * e.fn * Cb.m[a][c];
     }
-    for (int a = 0; a < 3; ++a)
-      for (int c = 0; c < 3; ++c) Ad[a][c] = D4 * e.dx * Cb.m[a][c];
     if (fits)
       col_store(S, pos, sc, vb, Ad);
     else
       direct_scatter<false>(e, sc, vb, Ad, 0.f, gcot);
+    // x: with vg = v_i (vbar + Ad d) per node, sums of grad W vg and of W v_i, axis by axis as in gather_v
     const StencilAddr sa = stencil_addr(e, sc.b);
     const float* genv = grid + (int64_t)e.tile_off * 512 + G1;
-    float xb[3] = {cx[0], cx[1], cx[2]};
-    float sv[3] = {0.f, 0.f, 0.f};   // sum of W v_i
-    float gz[3];                     // the z factor of grad W
-    for (int o = 0; o < 3; ++o) gz[o] = e.fn * sc.dw[2][o];
+    float gx[3] = {0.f, 0.f, 0.f}, sv[3] = {0.f, 0.f, 0.f};
 #pragma unroll 1
-    for (int ox = 0; ox < 3; ++ox)
+    for (int ox = 0; ox < 3; ++ox) {
+      const uint32_t ax = ox == 0 ? sa.x[0] : (ox == 1 ? sa.x[1] : sa.x[2]);
+      float wx, dwx;
+      spline_piece(ox, sc.f[0], wx, dwx);
+      const float d0 = (float)ox - sc.f[0];
+      float g0[3], yv[3] = {0.f, 0.f, 0.f}, yx = 0.f, yy = 0.f, yz = 0.f;
+      for (int a = 0; a < 3; ++a) g0[a] = fmaf(Ad[a][0], d0, vb[a]);
 #pragma unroll 1
       for (int oy = 0; oy < 3; ++oy) {
-        const uint32_t axy = (ox == 0 ? sa.x[0] : (ox == 1 ? sa.x[1] : sa.x[2])) +
-                             (oy == 0 ? sa.y[0] : (oy == 1 ? sa.y[1] : sa.y[2]));
+        const uint32_t axy = ax + (oy == 0 ? sa.y[0] : (oy == 1 ? sa.y[1] : sa.y[2]));
         float4 v4[3];
 #pragma unroll
         for (int oz = 0; oz < 3; ++oz) v4[oz] = ld4(genv + (axy + sa.z[oz]));
-        // column invariants: the x/y weight factors and vbar + D4 Cbar d at d_z = 0
-        float wx, wy, dwx, dwy;
-        spline_piece(ox, sc.f[0], wx, dwx);
+        float wy, dwy;
         spline_piece(oy, sc.f[1], wy, dwy);
-        const float wxy = wx * wy, gx = e.fn * dwx * wy, gy = e.fn * wx * dwy;
-        const float d0 = (float)ox - sc.f[0], d1 = (float)oy - sc.f[1];
-        float gc[3];
-        for (int a = 0; a < 3; ++a) gc[a] = fmaf(Ad[a][0], d0, fmaf(Ad[a][1], d1, vb[a]));
+        const float d1 = (float)oy - sc.f[1];
+        float gc[3], cs[3] = {0.f, 0.f, 0.f}, s0 = 0.f, s1 = 0.f;
+        for (int a = 0; a < 3; ++a) gc[a] = fmaf(Ad[a][1], d1, g0[a]);
 #pragma unroll
         for (int oz = 0; oz < 3; ++oz) {
-          const float wz = sc.w[2][oz], W = wxy * wz, d2 = (float)oz - sc.f[2];
-          const float gW[3] = {gx * wz, gy * wz, wxy * gz[oz]};
           const float vi[3] = {v4[oz].x, v4[oz].y, v4[oz].z};
-          float vg = 0.f;
-          for (int a = 0; a < 3; ++a) vg = fmaf(vi[a], fmaf(Ad[a][2], d2, gc[a]), vg);
-          for (int a = 0; a < 3; ++a) {
-            xb[a] = fmaf(gW[a], vg, xb[a]);
-            sv[a] = fmaf(W, vi[a], sv[a]);
-          }
+          const float dz = (float)oz - sc.f[2];
+          float vg = vi[0] * fmaf(Ad[0][2], dz, gc[0]);
+          vg = fmaf(vi[1], fmaf(Ad[1][2], dz, gc[1]), vg);
+          vg = fmaf(vi[2], fmaf(Ad[2][2], dz, gc[2]), vg);
+          s0 = fmaf(sc.w[2][oz], vg, s0);
+          s1 = fmaf(sc.dw[2][oz], vg, s1);
+          for (int a = 0; a < 3; ++a) cs[a] = fmaf(sc.w[2][oz], vi[a], cs[a]);
         }
+        yx = fmaf(wy, s0, yx);
+        yy = fmaf(dwy, s0, yy);
+        yz = fmaf(wy, s1, yz);
+        for (int a = 0; a < 3; ++a) yv[a] = fmaf(wy, cs[a], yv[a]);
       }
-    // the stencil sum of -D4 W Cbar^T v_i is -D4 Cbar^T sv
-    for (int a = 0; a < 3; ++a) xb[a] -= D4 * (Cb.m[0][a] * sv[0] + Cb.m[1][a] * sv[1] + Cb.m[2][a] * sv[2]);
-    for (int a = 0; a < 3; ++a) part[a * N + p] = xb[a];
+      gx[0] = fmaf(dwx, yx, gx[0]);
+      gx[1] = fmaf(wx, yy, gx[1]);
+      gx[2] = fmaf(wx, yz, gx[2]);
+      for (int a = 0; a < 3; ++a) sv[a] = fmaf(wx, yv[a], sv[a]);
+    }
+    // grad W = n dw, and the stencil sum of -4 n^2 W Cbar^T v_i is -n Ad^T sv
+    float xb[3];
+    for (int a = 0; a < 3; ++a)
+      xb[a] = fmaf(e.fn, gx[a] - (Ad[0][a] * sv[0] + Ad[1][a] * sv[1] + Ad[2][a] * sv[2]), cx[a]);
+    st_v3(part, N, t, 0, xb);
   }
   if (fits) col_scatter<false, BOXN>(e, S, 0.f, gcot);
 }
@@ -730,7 +809,7 @@ MD void g2p_adjoint_body(const EnvDev& e, int mat, bool valid, int64_t p, const 
 // cotangent pass through.
 // ----------------------------------------------------------------------------
 template <int BOXN, int MAT>
-__global__ void __launch_bounds__(256) k_p2g_col(const float* __restrict__ st, int64_t N,
+__global__ void __launch_bounds__(256, waves_per_simd<BOXN>()) k_p2g_col(const float* __restrict__ st, int64_t N,
                                                  const EnvDev* __restrict__ envs, const WorkItem* __restrict__ items,
                                                  float* __restrict__ grid, uint32_t* __restrict__ flags,
                                                  int32_t* __restrict__ errs, int k_call) {
@@ -739,13 +818,14 @@ __global__ void __launch_bounds__(256) k_p2g_col(const float* __restrict__ st, i
   const EnvDev& e = envs[it.env];
   if (k_call >= e.nsub) return;
   const bool valid = (int)threadIdx.x < it.count;
-  const int64_t p = it.start + (valid ? threadIdx.x : 0);
+  const uint32_t t = valid ? threadIdx.x : 0;
+  st += it.start;
   float x[3];
-  load_x3(st, N, p, x);
+  load_x3(st, N, t, x);
   p2g_col_body<BOXN>(e, MAT >= 0 ? MAT : e.material, valid, x, [&](float v[3], M3& Cm, M3& H) {
-    for (int a = 0; a < 3; ++a) v[a] = st[(3 + a) * N + p];
-    Cm = ld_m3(st, N, p, 6);
-    H = ld_m3(st, N, p, 15);
+    ld_v3(st, N, t, 3, v);
+    Cm = ld_m3(st, N, t, 6);
+    H = ld_m3(st, N, t, 15);
   }, grid, flags, errs + it.env, S);
 }
 
@@ -756,25 +836,27 @@ __global__ void __launch_bounds__(256) k_g2p(const float* __restrict__ st, float
   const WorkItem it = items[blockIdx.x];
   if ((int)threadIdx.x >= it.count) return;
   const EnvDev& e = envs[it.env];
-  const int64_t p = it.start + threadIdx.x;
+  const uint32_t t = threadIdx.x;
+  st += it.start;
+  out += it.start;
   if (k_call >= e.nsub) {
-    for (int c = 0; c < 24; ++c) out[c * N + p] = st[c * N + p];
+    copy_rows(st, out, N, t);
     return;
   }
   float x[3], xn[3], vn[3];
-  load_x3(st, N, p, x);
-  const M3 H = ld_m3(st, N, p, 15);
+  load_x3(st, N, t, x);
+  const M3 H = ld_m3(st, N, t, 15);
   M3 Cn;
   gather_v(e, grid, x, vn, Cn);
   for (int a = 0; a < 3; ++a) xn[a] = fmaf(e.dt, vn[a], x[a]);
-  store_new_state(out, N, p, xn, vn, Cn, project(e, trial_h(e, Cn, H), MAT >= 0 ? MAT : e.material), errs + it.env);
+  store_new_state(out, N, t, xn, vn, Cn, project(e, trial_h(e, Cn, H), MAT >= 0 ? MAT : e.material), errs + it.env);
 }
 
 // G2P of substep k fused with P2G of substep k + 1: the new state goes to the
 // tape once and is scattered from registers. k_call is substep k's call index;
 // an env frozen at k copies its state, one frozen at k + 1 only takes the G2P.
 template <int BOXN, int MAT>
-__global__ void __launch_bounds__(256) k_g2p2g_col(const float* __restrict__ st, float* __restrict__ out, int64_t N,
+__global__ void __launch_bounds__(256, waves_per_simd<BOXN>()) k_g2p2g_col(const float* __restrict__ st, float* __restrict__ out, int64_t N,
                                                    const EnvDev* __restrict__ envs,
                                                    const WorkItem* __restrict__ items,
                                                    const float* __restrict__ grid_in, float* __restrict__ grid_out,
@@ -785,22 +867,23 @@ __global__ void __launch_bounds__(256) k_g2p2g_col(const float* __restrict__ st,
   const EnvDev& e = envs[it.env];
   const int mat = MAT >= 0 ? MAT : e.material;
   const bool valid = (int)threadIdx.x < it.count;
-  const int64_t p = it.start + (valid ? threadIdx.x : 0);
+  const uint32_t t = valid ? threadIdx.x : 0;
+  st += it.start;
+  out += it.start;
   if (k_call >= e.nsub) {
-    if (valid)
-      for (int c = 0; c < 24; ++c) out[c * N + p] = st[c * N + p];
+    if (valid) copy_rows(st, out, N, t);
     return;
   }
   float x[3], xn[3], vn[3] = {0.f, 0.f, 0.f};
   M3 Cn = m3_zero(), Hn = m3_zero();
-  load_x3(st, N, p, x);
+  load_x3(st, N, t, x);
   if (valid) {
-    const M3 H = ld_m3(st, N, p, 15);
+    const M3 H = ld_m3(st, N, t, 15);
     gather_v(e, grid_in, x, vn, Cn);
     Hn = project(e, trial_h(e, Cn, H), mat);
   }
   for (int a = 0; a < 3; ++a) xn[a] = fmaf(e.dt, vn[a], x[a]);
-  if (valid) store_new_state(out, N, p, xn, vn, Cn, Hn, errs + it.env);
+  if (valid) store_new_state(out, N, t, xn, vn, Cn, Hn, errs + it.env);
   if (k_call + 1 >= e.nsub) return;   // the env stops after this substep (uniform over the block)
   p2g_col_body<BOXN>(e, mat, valid, xn, [&](float v[3], M3& Cm, M3& H) {
     for (int a = 0; a < 3; ++a) v[a] = vn[a];
@@ -810,7 +893,7 @@ __global__ void __launch_bounds__(256) k_g2p2g_col(const float* __restrict__ st,
 }
 
 template <int BOXN, int MAT>
-__global__ void __launch_bounds__(256) k_g2p_adjoint_col(const float* __restrict__ st,
+__global__ void __launch_bounds__(256, waves_per_simd<BOXN>()) k_g2p_adjoint_col(const float* __restrict__ st,
                                                          const float* __restrict__ st_next,
                                                          const float* __restrict__ cot, float* __restrict__ part,
                                                          int64_t N, const EnvDev* __restrict__ envs,
@@ -822,12 +905,14 @@ __global__ void __launch_bounds__(256) k_g2p_adjoint_col(const float* __restrict
   const EnvDev& e = envs[it.env];
   if (k_call >= e.nsub) return;
   const bool valid = (int)threadIdx.x < it.count;
-  const int64_t p = it.start + (valid ? threadIdx.x : 0);
+  const uint32_t t = valid ? threadIdx.x : 0;
+  cot += it.start;
   float pb[PB_COUNT] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
   float cx[3], cv[3];
-  for (int a = 0; a < 3; ++a) { cx[a] = cot[a * N + p]; cv[a] = cot[(3 + a) * N + p]; }
-  g2p_adjoint_body<BOXN>(e, MAT >= 0 ? MAT : e.material, valid, p, st, st_next, N, cx, cv, ld_m3(cot, N, p, 6),
-                         ld_m3(cot, N, p, 15), part, grid, gcot, pb, S);
+  ld_v3(cot, N, t, 0, cx);
+  ld_v3(cot, N, t, 3, cv);
+  g2p_adjoint_body<BOXN>(e, MAT >= 0 ? MAT : e.material, valid, t, st + it.start, st_next + it.start, N, cx, cv,
+                         ld_m3(cot, N, t, 6), ld_m3(cot, N, t, 15), part + it.start, grid, gcot, pb, S);
   block_reduce_params(pb, pacc + (int64_t)it.env * 8);
 }
 
@@ -841,20 +926,22 @@ k_p2g_adjoint(const float* __restrict__ st, const float* __restrict__ part, floa
   const WorkItem it = items[blockIdx.x];
   const EnvDev& e = envs[it.env];
   const bool valid = (int)threadIdx.x < it.count;
-  const int64_t p = it.start + (valid ? threadIdx.x : 0);
+  const uint32_t t = valid ? threadIdx.x : 0;
+  cot_out += it.start;
   if (k_call >= e.nsub) {
-    if (valid)
-      for (int c = 0; c < 24; ++c) cot_out[c * N + p] = cot_in[c * N + p];
+    if (valid) copy_rows(cot_in + it.start, cot_out, N, t);
     return;
   }
   float pb[PB_COUNT] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
   if (valid) {
     float cx[3], cv[3];
     M3 cC, cF;
-    p2g_adjoint_particle<MAT>(e, MAT >= 0 ? MAT : e.material, st, part, N, p, gcot, eig, pb, cx, cv, cC, cF);
-    for (int a = 0; a < 3; ++a) { cot_out[a * N + p] = cx[a]; cot_out[(3 + a) * N + p] = cv[a]; }
-    st_m3(cot_out, N, p, 6, cC);
-    st_m3(cot_out, N, p, 15, cF);
+    p2g_adjoint_particle<MAT>(e, MAT >= 0 ? MAT : e.material, st + it.start, part + it.start, N, t, gcot, eig, pb, cx,
+                              cv, cC, cF);
+    st_v3(cot_out, N, t, 0, cx);
+    st_v3(cot_out, N, t, 3, cv);
+    st_m3(cot_out, N, t, 6, cC);
+    st_m3(cot_out, N, t, 15, cF);
   }
   block_reduce_params(pb, pacc + (int64_t)it.env * 8);
 }
@@ -879,23 +966,28 @@ k_adj_pair_col(const float* __restrict__ st_prev, const float* __restrict__ st, 
   const int mat = MAT >= 0 ? MAT : e.material;
   if (k_call - 1 >= e.nsub) return;
   const bool valid = (int)threadIdx.x < it.count;
-  const int64_t p = it.start + (valid ? threadIdx.x : 0);
+  const uint32_t t = valid ? threadIdx.x : 0;
+  st_prev += it.start;
+  st += it.start;
+  part += it.start;
+  cot_end += it.start;
   float pb[PB_COUNT] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
   float cx[3] = {0.f, 0.f, 0.f}, cv[3] = {0.f, 0.f, 0.f};
   M3 cC = m3_zero(), cF = m3_zero();
   if (valid) {
     if (k_call >= e.nsub) {
-      for (int a = 0; a < 3; ++a) { cx[a] = cot_end[a * N + p]; cv[a] = cot_end[(3 + a) * N + p]; }
-      cC = ld_m3(cot_end, N, p, 6);
-      cF = ld_m3(cot_end, N, p, 15);
+      ld_v3(cot_end, N, t, 0, cx);
+      ld_v3(cot_end, N, t, 3, cv);
+      cC = ld_m3(cot_end, N, t, 6);
+      cF = ld_m3(cot_end, N, t, 15);
     } else {
       // the eigen-decomposition waits in the payload rows, which are written only after col_index's barriers
       static_assert(sizeof(S.pay) >= 12 * kItem * sizeof(float), "eigen stash exceeds the payload rows");
-      p2g_adjoint_particle<MAT>(e, mat, st, part, N, p, gcot, reinterpret_cast<float(*)[kItem]>(S.pay), pb, cx, cv, cC,
+      p2g_adjoint_particle<MAT>(e, mat, st, part, N, t, gcot, reinterpret_cast<float(*)[kItem]>(S.pay), pb, cx, cv, cC,
                                 cF);
     }
   }
-  g2p_adjoint_body<BOXN>(e, mat, valid, p, st_prev, st, N, cx, cv, cC, cF, part, grid_prev, gcot, pb, S);
+  g2p_adjoint_body<BOXN>(e, mat, valid, t, st_prev, st, N, cx, cv, cC, cF, part, grid_prev, gcot, pb, S);
   block_reduce_params(pb, pacc + (int64_t)it.env * 8);
 }
 

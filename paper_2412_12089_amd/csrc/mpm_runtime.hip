@@ -108,7 +108,7 @@ struct mpm_batch {
   // substep instead of twice, and were the faster ones on every batch timed
   // (16 to 12,500 blocks, 1 to 8 particles per cell).
   int var_p2g = 2, var_g2p_adj = 2;
-  int box = 0;        // LDS box budget of the column scatter: 0 = 1024 nodes, 1 = 384 nodes
+  int box = 0;        // LDS box budget of the column scatter: 0 = 1024 nodes, 1 = 640 nodes
   int specialize = 1; // 1 = one launch per material, compiled for it; 0 = one generic launch
   int fuse = 1;       // 1: G2P of substep k and P2G of substep k + 1 in one kernel
   int fuse_adj = 1;   // 1: P2G adjoint of substep k and G2P adjoint of substep k - 1 in one kernel
