@@ -12,6 +12,12 @@ constexpr int kFemPrm = 8;         // mu, lam, rho, damp, k_e, k_d, k_f, z_g
 struct FemMesh {
   int E, n, T;
   const int4* tets;       // [T] node indices
+  // the substep kernels' own order of the nodes (by element count, the most first) and each node's row of
+  // slots for its elements' forces
+  const ushort4* ptets;   // [T] corners' places in that order
+  const ushort4* slots;   // [T] corners' slots
+  const int4* rows;       // [n] node, first slot, slots in use
+  int P;                  // slots in all
   const int32_t* inc_off; // [n + 1] node -> incidence range
   const int32_t* inc;     // [4 T] incidences: tet * 4 + corner
   const float* Bm;        // [E][T][9] D_m^-1, row-major
@@ -27,7 +33,7 @@ struct FemMesh {
 void launch_fem_rest(const FemMesh& m, const float* X, float* Bm, float* W, float* wm, int32_t* bad, hipStream_t s);
 
 // S substeps of every env from (x, v) [E][n][3] in place; act [S][E][T] or null; with tape non-null, the
-// states [S + 1][E][n][6] (x then v per node) and the activations [S][E][T] are kept
+// states [S + 1][E][6][n] (x then v, nodes in the kernels' order) and the activations [S][E][T] are kept
 void launch_fem_forward(const FemMesh& m, int S, float* x, float* v, const float* act, float* tape,
                         float* tape_act, int32_t* errs, hipStream_t s);
 
@@ -36,8 +42,8 @@ void launch_fem_forward(const FemMesh& m, int S, float* x, float* v, const float
 void launch_fem_backward(const FemMesh& m, int S, const float* tape, const float* tape_act, const float* gx,
                          const float* gv, float* dx0, float* dv0, float* dact, double* dprm, hipStream_t s);
 
-// LDS bytes of the forward / backward block of a mesh size
-size_t fem_forward_lds(int n, int T);
-size_t fem_backward_lds(int n, int T);
+// LDS bytes of the forward / backward block for n nodes and P slots
+size_t fem_forward_lds(int n, int P);
+size_t fem_backward_lds(int n, int P);
 
 }  // namespace mpmx

@@ -1,7 +1,8 @@
 // Host side of the FEM batch (include/mpm_fem.h): validation, device memory,
-// the node -> element incidences of the shared topology, launches.
+// the node -> element incidences and force slots of the shared topology, launches.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cmath>
 #include <cstring>
 #include <string>
@@ -23,6 +24,10 @@ struct mpm_fem {
   std::string err;
 
   int4* tets = nullptr;
+  ushort4* ptets = nullptr;
+  ushort4* slots = nullptr;
+  int4* rows = nullptr;
+  int P = 0;
   int32_t* inc_off = nullptr;
   int32_t* inc = nullptr;
   float* Bm[2] = {nullptr, nullptr};   // rest data is double-buffered: a degenerate mesh leaves the old one
@@ -33,7 +38,7 @@ struct mpm_fem {
   float* prm = nullptr;                 // [E][8] FP32 copy of the parameters
   float* x = nullptr;
   float* v = nullptr;
-  float* tape = nullptr;                // [(max_S + 1)][E][n][6]
+  float* tape = nullptr;                // [(max_S + 1)][E][6][n]
   float* tape_act = nullptr;            // [max_S][E][T]
   int32_t* errs = nullptr;
   int32_t* bad = nullptr;
@@ -88,6 +93,10 @@ mpmx::FemMesh mesh_of(const mpm_fem* f) {
   m.n = f->n;
   m.T = f->T;
   m.tets = f->tets;
+  m.ptets = f->ptets;
+  m.slots = f->slots;
+  m.rows = f->rows;
+  m.P = f->P;
   m.inc_off = f->inc_off;
   m.inc = f->inc;
   m.Bm = f->Bm[f->cur];
@@ -136,8 +145,27 @@ int mpm_fem_create(const mpm_fem_desc* d, const int32_t* tets, const mpm_allocat
   std::vector<int> fill(off.begin(), off.end() - 1);
   for (int t = 0; t < T; ++t)
     for (int c = 0; c < 4; ++c) inc[fill[tets[4 * t + c]]++] = t * 4 + c;
+  // the substep kernels' nodes: the ones with the most elements first, each with a row of slots, one per
+  // incidence, of odd pitch
+  std::vector<int32_t> order(n);
+  for (int i = 0; i < n; ++i) order[i] = i;
+  std::stable_sort(order.begin(), order.end(), [&](int a, int b) { return off[a + 1] - off[a] > off[b + 1] - off[b]; });
+  std::vector<int4> rows(n);
+  std::vector<ushort4> ptets(T), slots(T);
+  int P = 0;
+  for (int q = 0; q < n; ++q) {
+    const int i = order[q], deg = off[i + 1] - off[i];
+    rows[q] = make_int4(i, P, deg, 0);
+    for (int k = 0; k < deg; ++k) {
+      const int t = inc[off[i] + k] >> 2, c = inc[off[i] + k] & 3;
+      (&ptets[t].x)[c] = (unsigned short)q;
+      (&slots[t].x)[c] = (unsigned short)(P + k);
+    }
+    P += deg | 1;
+  }
 
   mpm_fem* f = new mpm_fem();
+  f->P = P;
   f->E = d->n_envs;
   f->n = n;
   f->T = T;
@@ -151,6 +179,9 @@ int mpm_fem_create(const mpm_fem_desc* d, const int32_t* tets, const mpm_allocat
   }
   const size_t E = f->E;
   f->tets = (int4*)falloc(f, sizeof(int4) * T);
+  f->ptets = (ushort4*)falloc(f, sizeof(ushort4) * T);
+  f->slots = (ushort4*)falloc(f, sizeof(ushort4) * T);
+  f->rows = (int4*)falloc(f, sizeof(int4) * n);
   f->inc_off = (int32_t*)falloc(f, sizeof(int32_t) * (n + 1));
   f->inc = (int32_t*)falloc(f, sizeof(int32_t) * 4 * T);
   for (int b = 0; b < 2; ++b) {
@@ -165,7 +196,7 @@ int mpm_fem_create(const mpm_fem_desc* d, const int32_t* tets, const mpm_allocat
   f->tape_act = (float*)falloc(f, sizeof(float) * E * T * (size_t)(f->max_S > 0 ? f->max_S : 1));
   f->errs = (int32_t*)falloc(f, sizeof(int32_t) * E);
   f->bad = (int32_t*)falloc(f, sizeof(int32_t));
-  bool ok = f->tets && f->inc_off && f->inc && f->prm && f->x && f->v && f->tape && f->tape_act && f->errs && f->bad;
+  bool ok = f->tets && f->ptets && f->slots && f->rows && f->inc_off && f->inc && f->prm && f->x && f->v && f->tape && f->tape_act && f->errs && f->bad;
   for (int b = 0; b < 2; ++b) ok = ok && f->Bm[b] && f->W[b] && f->wm[b];
   if (!ok) {
     free_all(f);
@@ -179,6 +210,9 @@ int mpm_fem_create(const mpm_fem_desc* d, const int32_t* tets, const mpm_allocat
     std::memcpy(&prm[MPM_FEM_PARAMS * e], row, sizeof row);
   }
   hipError_t e1 = hipMemcpyAsync(f->tets, tets, sizeof(int4) * T, hipMemcpyHostToDevice, f->stream);
+  if (e1 == hipSuccess) e1 = hipMemcpyAsync(f->ptets, ptets.data(), sizeof(ushort4) * T, hipMemcpyHostToDevice, f->stream);
+  if (e1 == hipSuccess) e1 = hipMemcpyAsync(f->slots, slots.data(), sizeof(ushort4) * T, hipMemcpyHostToDevice, f->stream);
+  if (e1 == hipSuccess) e1 = hipMemcpyAsync(f->rows, rows.data(), sizeof(int4) * n, hipMemcpyHostToDevice, f->stream);
   if (e1 == hipSuccess) e1 = hipMemcpyAsync(f->inc_off, off.data(), sizeof(int32_t) * (n + 1), hipMemcpyHostToDevice, f->stream);
   if (e1 == hipSuccess) e1 = hipMemcpyAsync(f->inc, inc.data(), sizeof(int32_t) * 4 * T, hipMemcpyHostToDevice, f->stream);
   if (e1 == hipSuccess) e1 = hipMemcpyAsync(f->prm, prm.data(), sizeof(float) * prm.size(), hipMemcpyHostToDevice, f->stream);
