@@ -17,6 +17,7 @@ struct RbModel {
   const uint64_t* desc;     // [N] bit k: link k is in the subtree of link i (i included)
   const uint64_t* kids;     // [N] bit k: link k's parent is link i
   const int32_t* level;     // [N] height (longest path down to a leaf) | depth (joints above) << 16
+  const uint64_t* hmask;    // [H] bit k: link k has height h
   int H, D;                 // height and depth levels
   const int32_t* cbeg;      // [N + 1] contact range of each link
   const float* contact;     // [C][4] sphere centre (link frame), radius
@@ -30,13 +31,13 @@ struct RbModel {
 int rb_group(int N);
 
 // S substeps of every env from (q, qd) [E][N] in place; tau [S][E][N] or null; with tape non-null, the states
-// [S + 1][E][2][N] (q then qd) and the joint accelerations [S][E][N] are kept
-void launch_rb_forward(const RbModel& m, int S, float* q, float* qd, const float* tau, float* tape, float* tape_qdd,
+// [S + 1][E][2][N] (q then qd) and the torques [S][E][N] are kept
+void launch_rb_forward(const RbModel& m, int S, float* q, float* qd, const float* tau, float* tape, float* tape_tau,
                        int32_t* errs, hipStream_t s);
 
 // reverse mode over the S recorded substeps: (gq, gqd) cotangents of the final state (null = 0), out:
 // dq0, dqd0 [E][N], dtau [S][E][N] (or null), dprm [E][kRbPrm] doubles (or null)
-void launch_rb_backward(const RbModel& m, int S, const float* tape, const float* tape_qdd, const float* gq,
+void launch_rb_backward(const RbModel& m, int S, const float* tape, const float* tape_tau, const float* gq,
                         const float* gqd, float* dq0, float* dqd0, float* dtau, double* dprm, hipStream_t s);
 
 }  // namespace mpmx

@@ -1,6 +1,6 @@
 // Articulated rigid bodies on a fixed base (Appendix D.1): the batched forward
 // substeps (composite rigid body algorithm for the mass matrix, recursive
-// Newton-Euler for the bias forces, a sparse solve, semi-implicit Euler) and
+// Newton-Euler for the bias forces, a sparse Cholesky solve, semi-implicit Euler) and
 // their reverse-mode adjoint.
 //
 // One environment per group of G lanes of a wave (G: the link count rounded up
@@ -8,33 +8,21 @@
 // barriers are cheap. Every spatial quantity is a world-frame Plucker vector
 // about one fixed origin (motion: angular velocity, velocity of the body point
 // at the origin; force: moment about the origin, force). In that frame the
-// tree recursions need no coordinate transforms:
-//  - poses and root-path sums (velocities, accelerations) are taken by pointer
-//    doubling: round k combines a lane's partial result with that of its 2^k-th
-//    ancestor through a lane permute, ceil(log2 D) rounds for a tree D deep;
-//  - subtree sums (forces, composite inertias) go children first over the tree's
-//    height levels through LDS, a lane's running sum staying in registers;
-//  - the joint-space mass matrix M_ij = S_j . (Ic_i S_i), j on i's root path,
-//    is kept as one row per link with its ancestors in order of depth, so the
-//    ancestors that two links of a path share have the same places in both rows.
-//    Eliminated leaves first (M = L^T P L, L unit triangular) it keeps its sparsity, and
-//    eliminating link k from its ancestor i's row is one dense multiply-add
-//    of the leading part of row k, 128 bits at a time. The right-hand side is
-//    eliminated along with the rows; the solve with L goes down one depth at a
-//    time, each lane taking its one ancestor there through a lane permute.
-// A substep touches HBM only for the torques and the tape. The adjoint reads
-// the recorded joint accelerations and so needs one elimination, with the
-// cotangent as right-hand side, and no bias forces.
-//
-// Bound by instruction issue once the chip is full (65536 hands of 13 links: the
-// vector ALUs were busy 81% of the time), by their chain when it is not. Walking
-// root paths and subtrees by 64-bit link masks, with a factorisation and solves
-// over them, 16 substeps of those hands took 951 us forward and 1809 us back;
-// 595 and 990 now. 256 hands: 146 and 263 us; 91 and 138 now.
+// tree recursions need no coordinate transforms: a link's velocity and
+// acceleration are sums over the joints on its root path, its subtree force
+// and composite inertia are sums over its subtree, and each lane takes those
+// sums from LDS (through the link's ancestor bit mask, and children first over
+// the tree's height levels). The
+// joint-space mass matrix is M_ij = S_j . (Ic_i S_i) for j on i's root path
+// and zero between different branches. Factorised leaves first, M = L^T L
+// keeps that sparsity (no fill-in: eliminating a link touches only its root
+// path), so the factorisation and the solve with L^T run one tree height level
+// at a time and the solve with L one depth level at a time: a barrier per
+// level instead of one per joint. A substep touches HBM only for the torques
+// and the tape.
 #include <hip/hip_runtime.h>
 
 #include <cmath>
-#include <type_traits>
 
 #include "mpm_device.h"
 #include "rb_kernels.h"
@@ -126,38 +114,16 @@ MD V6 iapply(const Inertia& I, const V6& a) {
   return r;
 }
 
-// link sets as bit masks: 32 bits where they suffice (a 64-bit set costs its walk
-// about five more instructions per link)
-template <int G>
-using Mask = std::conditional_t<(G <= 32), uint32_t, uint64_t>;
-MD int first_bit(uint32_t m) { return __builtin_ctz(m); }
-MD int first_bit(uint64_t m) { return __builtin_ctzll(m); }
-MD int last_bit(uint32_t m) { return 31 - __builtin_clz(m); }
-MD int last_bit(uint64_t m) { return 63 - __builtin_clzll(m); }
-
-MD float lane_read(float x, int addr) {   // x of the lane at byte address `addr` (lane * 4); every lane takes part
-  return __builtin_bit_cast(float, __builtin_amdgcn_ds_bpermute(addr, __builtin_bit_cast(int, x)));
-}
-
-constexpr int rounds_max(int G) { return G == 8 ? 3 : G == 16 ? 4 : G == 32 ? 5 : 6; }
-
 // a lane's own link
-template <int G>
 struct Link {
   float Rt[9], pt[3], ax[3], m, com[3], In[6];
-  float ct[4];                 // its first contact sphere
-  Mask<G> anc, desc, kids;
-  int up[rounds_max(G)];       // byte address of the lane of the 2^k-th ancestor, the lane's own where there is none
-  int nup;                     // how many of them there are: depth >= 2^k for k < nup
-  int c0;                      // first lane of the environment
+  uint64_t anc, desc, kids;
   int cb, ce;
   int height, depth;   // levels: longest path down to a leaf, joints above
   bool prism;          // the joint slides along its axis instead of turning about it
 };
-template <int G>
-MD Link<G> load_link(const RbModel& M, int i, int c0, bool live) {
-  Link<G> l;
-  l.c0 = c0;
+MD Link load_link(const RbModel& M, int i, bool live) {
+  Link l;
   const float* s = M.link + (size_t)(live ? i : 0) * kRbLinkF;
 #pragma unroll
   for (int k = 0; k < 9; ++k) l.Rt[k] = s[k];
@@ -170,31 +136,14 @@ MD Link<G> load_link(const RbModel& M, int i, int c0, bool live) {
   l.m = s[15];
 #pragma unroll
   for (int k = 0; k < 6; ++k) l.In[k] = s[19 + k];
-  l.anc = live ? (Mask<G>)M.anc[i] : 0;
-  l.desc = live ? (Mask<G>)M.desc[i] & ~((Mask<G>)1 << i) : 0;
-  l.kids = live ? (Mask<G>)M.kids[i] : 0;
+  l.anc = live ? M.anc[i] : 0ull;
+  l.desc = live ? M.desc[i] : 0ull;
+  l.kids = live ? M.kids[i] : 0ull;
   l.cb = live ? M.cbeg[i] : 0;
   l.ce = live ? M.cbeg[i + 1] : 0;
   l.height = live ? (M.level[i] & 0xffff) : -1;
   l.depth = live ? (M.level[i] >> 16) : -1;
   l.prism = s[25] != 0.f;
-#pragma unroll
-  for (int k = 0; k < 4; ++k) l.ct[k] = l.cb < l.ce ? M.contact[(size_t)l.cb * 4 + k] : 0.f;
-  // 2^k-th ancestors: the parent is the last link above i on its root path (parents come first)
-  const Mask<G> above = l.anc & ~((Mask<G>)1 << i);
-  l.nup = 0;
-#pragma unroll
-  for (int k = 0; k < rounds_max(G); ++k) {
-    if (k == 0)
-      l.up[0] = (c0 + (above ? last_bit(above) : i)) * 4;
-    else
-      l.up[k] = __builtin_amdgcn_ds_bpermute(l.up[k - 1], l.up[k - 1]);
-    if (l.depth >= (1 << k)) {
-      l.nup = k + 1;
-    } else {
-      l.up[k] = (c0 + i) * 4;
-    }
-  }
   return l;
 }
 
@@ -210,101 +159,115 @@ MD Prm load_prm(const RbModel& M, int e) {
   return p;
 }
 
-// LDS of a block. A column per lane: rows of vectors being summed over subtrees
-// (quads of rows side by side, so that a lane moves 128 bits at a time), joint
-// motions, mass-matrix rows. The sums are finished before the mass matrix
-// is written and it is used up before the next ones, so the two share their space.
-typedef float f4 __attribute__((ext_vector_type(4), may_alias));
-typedef float f2 __attribute__((ext_vector_type(2), may_alias));
+// LDS of a block. The environments' columns are interleaved (column
+// env * G + link of each row), so the four environments of a wave use
+// different banks when their lanes touch the same link. The joint blocks live
+// only while the lanes compose their poses; the inertias and the mass matrix
+// are written after the next barriers, so the two share their space.
 template <int G>
 struct BlockLds {
-  static constexpr int kRow = G + 4;   // a multiple of four, spread over the banks
+  float X[6][kBlock];   // exchange of 6-vectors (and the final parameter-cotangent reduction)
+  float Y[6][kBlock];
+  float dinv[kBlock];   // 1 / L_kk
+  float y[kBlock];      // substitution values
+  float x[kBlock];
   union {
-    f4 sum[4 * kBlock];
-    f4 row[kBlock * kRow / 4];
-  };
-  f4 S[6 * kBlock / 4];
-  f2 piv[kBlock];   // 1 / pivot and eliminated right-hand side of a link
+    float B[12][kBlock];   // per joint: joint_rot Rot(axis, q) (9), joint_pos (3)
+    struct {
+      float Ic[10][kBlock];                // body inertias, summed over subtrees
+      float M[kBlock / G][G][G + 1];       // per env, row i, entries j on i's root path: the mass matrix, then L
+    } cm;
+  } u;
 };
 
-// NR values of a lane (an even number) as a column
-template <int NR>
-MD void put_rows(f4* A, int col, const float (&a)[NR]) {
-#pragma unroll
-  for (int q = 0; q < NR / 4; ++q) A[q * kBlock + col] = f4{a[4 * q], a[4 * q + 1], a[4 * q + 2], a[4 * q + 3]};
-  if constexpr (NR % 4 == 2) reinterpret_cast<f2*>(A + NR / 4 * kBlock)[col] = f2{a[NR - 2], a[NR - 1]};
-}
-template <int NR>
-MD void get_rows(const f4* A, int col, float (&a)[NR]) {
-#pragma unroll
-  for (int q = 0; q < NR / 4; ++q) {
-    const f4 v = A[q * kBlock + col];
-#pragma unroll
-    for (int k = 0; k < 4; ++k) a[4 * q + k] = v[k];
-  }
-  if constexpr (NR % 4 == 2) {
-    const f2 v = reinterpret_cast<const f2*>(A + NR / 4 * kBlock)[col];
-    a[NR - 2] = v[0];
-    a[NR - 1] = v[1];
-  }
+// one environment's view of the block's LDS: row pointers offset to its columns
+template <int G>
+struct EnvLds {
+  float (*X)[kBlock];
+  float (*Y)[kBlock];
+  float (*B)[kBlock];
+  float (*Ic)[kBlock];
+  float (*M)[G + 1];
+  float *dinv, *y, *x;
+};
+template <int G>
+MD EnvLds<G> env_lds(BlockLds<G>& s, int grp) {
+  const int c0 = grp * G;
+  EnvLds<G> e;
+  e.X = reinterpret_cast<float(*)[kBlock]>(&s.X[0][c0]);
+  e.Y = reinterpret_cast<float(*)[kBlock]>(&s.Y[0][c0]);
+  e.B = reinterpret_cast<float(*)[kBlock]>(&s.u.B[0][c0]);
+  e.Ic = reinterpret_cast<float(*)[kBlock]>(&s.u.cm.Ic[0][c0]);
+  e.M = s.u.cm.M[grp];
+  e.dinv = s.dinv + c0;
+  e.y = s.y + c0;
+  e.x = s.x + c0;
+  return e;
 }
 
-// Subtree sums: a lane's own values on entry, the sums over its subtree on
-// return. One height level at a time a link adds its children's finished
-// columns, so a level costs the most children of any of its links (not the size
-// of the largest subtree).
-template <int G, int NR>
-MD void subtree_sums(const RbModel& M, const Link<G>& l, int col, bool live, f4* A, float (&a)[NR]) {
-  if (live) put_rows(A, col, a);
-  __syncthreads();
-  for (int h = 1; h < M.H; ++h) {
-    if (l.height == h) {
-      Mask<G> mk = l.kids;
-      while (mk) {
-        const int c = first_bit(mk);
-        mk &= mk - 1;
-        float v[NR];
-        get_rows(A, l.c0 + c, v);
+// sum of the 6-vectors of the links in a bit mask (a root path or a subtree), in ascending link order
+MD V6 mask_sum(const float (*A)[kBlock], uint64_t mk) {
+  V6 r = zero6();
+  while (mk) {
+    const int j = __builtin_ctzll(mk);
+    mk &= mk - 1;
 #pragma unroll
-        for (int k = 0; k < NR; ++k) a[k] += v[k];
+    for (int k = 0; k < 6; ++k) r.c[k] += A[k][j];
+  }
+  return r;
+}
+MD void put6(float (*A)[kBlock], int lane, const V6& v) {
+#pragma unroll
+  for (int k = 0; k < 6; ++k) A[k][lane] = v.c[k];
+}
+MD V6 get6(const float (*A)[kBlock], int j) {
+  V6 r;
+#pragma unroll
+  for (int k = 0; k < 6; ++k) r.c[k] = A[k][j];
+  return r;
+}
+
+// Subtree sums in place: every lane's column of the NA rows of A and the NB
+// rows of B holds its link's own values on entry (visible after a barrier) and
+// the sum over its subtree on return. One height level at a time, a link adds
+// its children's finished sums, so a level costs the most children of any of
+// its links (not the size of the largest subtree).
+template <int NA, int NB>
+MD void subtree_sums(const RbModel& M, const Link& l, int lane, bool live, float (*A)[kBlock], float (*B)[kBlock]) {
+  for (int h = 1; h < M.H; ++h) {
+    if (live && l.height == h) {
+      float a[NA], b[NB > 0 ? NB : 1];
+#pragma unroll
+      for (int k = 0; k < NA; ++k) a[k] = A[k][lane];
+#pragma unroll
+      for (int k = 0; k < NB; ++k) b[k] = B[k][lane];
+      uint64_t mk = l.kids;
+      while (mk) {
+        const int c = __builtin_ctzll(mk);
+        mk &= mk - 1;
+#pragma unroll
+        for (int k = 0; k < NA; ++k) a[k] += A[k][c];
+#pragma unroll
+        for (int k = 0; k < NB; ++k) b[k] += B[k][c];
       }
-      put_rows(A, col, a);
+#pragma unroll
+      for (int k = 0; k < NA; ++k) A[k][lane] = a[k];
+#pragma unroll
+      for (int k = 0; k < NB; ++k) B[k][lane] = b[k];
     }
     __syncthreads();
-  }
-}
-
-// sum of x over the links of the root path
-template <int G>
-MD void path_sum(const RbModel& M, const Link<G>& l, V6& x) {
-#pragma unroll
-  for (int k = 0; k < rounds_max(G); ++k) {
-    if ((1 << k) >= M.D) break;
-    float t[6];
-#pragma unroll
-    for (int c = 0; c < 6; ++c) t[c] = lane_read(x.c[c], l.up[k]);
-    if (k < l.nup) {
-#pragma unroll
-      for (int c = 0; c < 6; ++c) x.c[c] += t[c];
-    }
   }
 }
 
 // what the adjoint needs of one substep's forward, per lane
 struct Frame {
   float R[9], p[3];
-  V6 S, V, u, A;
+  V6 S, V, u, Ab, fext;
   Inertia I;
 };
 
-template <int G>
-MD void contact_point(const RbModel& M, const Link<G>& l, const Frame& F, int c, float* cw, float* x) {
-  float s[4] = {l.ct[0], l.ct[1], l.ct[2], l.ct[3]};
-  if (c > l.cb) {
-    const f4 v = reinterpret_cast<const f4*>(M.contact)[c];
-#pragma unroll
-    for (int k = 0; k < 4; ++k) s[k] = v[k];
-  }
+MD void contact_point(const RbModel& M, const Frame& F, int c, float* cw, float* x) {
+  const float* s = M.contact + (size_t)c * 4;
 #pragma unroll
   for (int a = 0; a < 3; ++a) cw[a] = F.p[a] + F.R[3 * a] * s[0] + F.R[3 * a + 1] * s[1] + F.R[3 * a + 2] * s[2];
   x[0] = cw[0];
@@ -312,115 +275,96 @@ MD void contact_point(const RbModel& M, const Link<G>& l, const Frame& F, int c,
   x[2] = cw[2] - s[3];
 }
 
-// Solves M x = b for the mass matrix M_ij = S_j . (Ic_i S_i); L.S holds every
-// lane's S. Row i has the ancestors' entries by depth, its own at l.depth.
-// Leaves first, one height level at a time: the level's links invert their
-// pivots, then every link above them eliminates them from its row and
-// right-hand side (row_i -= (M_ki / M_kk) row_k over i's root path). Rows a
-// level reads are never written in that level. Every lane of the block calls it.
+// Solves M x = b with M = L^T L in E.M / E.dinv: L^T y = b over the height
+// levels (y_k takes the subtree's y), then L x = y over the depth levels (x_k
+// takes the root path's x); b and x are per lane (lane < N).
 template <int G>
-MD float solve(const RbModel& M, const Link<G>& l, BlockLds<G>& L, int col, bool live, const Inertia& Ic,
-               const V6& S, float b) {
-  constexpr int kRow = BlockLds<G>::kRow;
-  float* row = reinterpret_cast<float*>(L.row) + col * kRow;
-  {
-    const V6 Fc = iapply(Ic, S);
-    Mask<G> mk = l.anc;
-    for (int d = 0; mk; ++d) {
-      const int j = first_bit(mk);
-      mk &= mk - 1;
-      float Sj[6];
-      get_rows(L.S, l.c0 + j, Sj);
-      float t = 0.f;
-#pragma unroll
-      for (int k = 0; k < 6; ++k) t = fmaf(Sj[k], Fc.c[k], t);
-      row[d] = t;
-    }
-  }
-  __syncthreads();
-  float inv = 0.f;
+MD float tree_solve(const RbModel& M, const Link& l, EnvLds<G>& E, int lane, bool live, float b) {
+  float y = 0.f;
   for (int h = 0; h < M.H; ++h) {
-    if (l.height == h) {
-      const float p = row[l.depth];
-      inv = p > 0.f ? 1.f / p : __builtin_nanf("");   // a non-positive pivot: the env is flagged non-finite
-      L.piv[col] = f2{inv, b};
-    }
-    __syncthreads();
-    // the links of height h (the same in every environment of the block)
-    Mask<G> mk = l.desc & (Mask<G>)__ballot(l.height == h);
-    while (mk) {
-      const int k = l.c0 + first_bit(mk);
-      mk &= mk - 1;
-      const f2 pk = L.piv[k];
-      const float* rk = reinterpret_cast<const float*>(L.row) + k * kRow;
-      const float lki = rk[l.depth] * pk[0];
-      b = fmaf(-lki, pk[1], b);
-      for (int d = 0; d <= l.depth; d += 4) {   // past l.depth: places that row i does not use
-        const f4 vk = *reinterpret_cast<const f4*>(rk + d);
-        f4 vi = *reinterpret_cast<f4*>(row + d);
-#pragma unroll
-        for (int c = 0; c < 4; ++c) vi[c] = fmaf(-lki, vk[c], vi[c]);
-        *reinterpret_cast<f4*>(row + d) = vi;
+    if (live && l.height == h) {
+      float t = b;
+      uint64_t mk = l.desc & ~(1ull << lane);
+      while (mk) {
+        const int c = __builtin_ctzll(mk);
+        mk &= mk - 1;
+        t = fmaf(-E.M[c][lane], E.y[c], t);
       }
+      y = t * E.dinv[lane];
+      E.y[lane] = y;
     }
     __syncthreads();
   }
-  // x_k = (b_k - sum over the ancestors j of M_kj x_j) / M_kk: a lane has its x once the depths above are done
-  Mask<G> rem = l.anc;
-  for (int d = 0; d + 1 < M.D; ++d) {
-    const float xj = lane_read(b * inv, (l.c0 + (rem ? first_bit(rem) : 0)) * 4);
-    if (l.depth > d) b = fmaf(-row[d], xj, b);
-    rem &= rem - 1;
+  float x = 0.f;
+  for (int d = 0; d < M.D; ++d) {
+    if (live && l.depth == d) {
+      float t = y;
+      uint64_t mk = l.anc & ~(1ull << lane);
+      while (mk) {
+        const int j = __builtin_ctzll(mk);
+        mk &= mk - 1;
+        t = fmaf(-E.M[lane][j], E.x[j], t);
+      }
+      x = t * E.dinv[lane];
+      E.x[lane] = x;
+    }
+    __syncthreads();
   }
-  __syncthreads();   // the rows' space is free
-  return live ? b * inv : 0.f;
+  return x;
 }
 
-// Poses, joint motions, inertias, velocities and accelerations of an environment's links at (q, qd) with joint
-// accelerations qdd (a sum over the root path of S_j qdd_j + V_j x S_j qd_j, and -g).
+// One substep's dynamics of an environment: fills F, leaves M's factor L in E and returns qdd of the
+// lane's joint. Every lane of the block calls it (barriers inside).
 template <int G>
-MD void kinematics(const RbModel& M, const Link<G>& l, float q, float qd, float qdd, Frame& F) {
-  // own joint: R = joint_rot Rot(axis, q) (Rodrigues: c I + s [a]x + (1 - c) a a^T) and p = joint_pos; a
+MD float dynamics(const RbModel& M, const Link& l, EnvLds<G>& E, int lane, bool live, float q, float qd, float tau,
+                  const Prm& P, Frame& F) {
+  // joint blocks B = joint_rot Rot(axis, q) (Rodrigues: c I + s [a]x + (1 - c) a a^T) and joint_pos; a
   // prismatic joint turns nothing (Rot = I) and shifts joint_pos by q joint_rot axis
   {
     float sn = 0.f, cs = 1.f;
     if (!l.prism) sincosf(q, &sn, &cs);
     const float* a = l.ax;
     const float oc = 1.f - cs;
-    const float Rq[9] = {cs + oc * a[0] * a[0], oc * a[0] * a[1] - sn * a[2], oc * a[0] * a[2] + sn * a[1],
-                         oc * a[1] * a[0] + sn * a[2], cs + oc * a[1] * a[1], oc * a[1] * a[2] - sn * a[0],
-                         oc * a[2] * a[0] - sn * a[1], oc * a[2] * a[1] + sn * a[0], cs + oc * a[2] * a[2]};
-#pragma unroll
-    for (int r = 0; r < 3; ++r)
-#pragma unroll
-      for (int c = 0; c < 3; ++c)
-        F.R[3 * r + c] = l.Rt[3 * r] * Rq[c] + l.Rt[3 * r + 1] * Rq[3 + c] + l.Rt[3 * r + 2] * Rq[6 + c];
-    const float qs = l.prism ? q : 0.f;
-#pragma unroll
-    for (int k = 0; k < 3; ++k)
-      F.p[k] = fmaf(qs, l.Rt[3 * k] * a[0] + l.Rt[3 * k + 1] * a[1] + l.Rt[3 * k + 2] * a[2], l.pt[k]);
-  }
-  // world pose: after round k a lane's pose is relative to its 2^(k+1)-th ancestor (or the world)
-#pragma unroll
-  for (int k = 0; k < rounds_max(G); ++k) {
-    if ((1 << k) >= M.D) break;
-    float R[9], p[3];
-#pragma unroll
-    for (int c = 0; c < 9; ++c) R[c] = lane_read(F.R[c], l.up[k]);
-#pragma unroll
-    for (int c = 0; c < 3; ++c) p[c] = lane_read(F.p[c], l.up[k]);
-    if (k < l.nup) {
+    float Rq[9] = {cs + oc * a[0] * a[0], oc * a[0] * a[1] - sn * a[2], oc * a[0] * a[2] + sn * a[1],
+                   oc * a[1] * a[0] + sn * a[2], cs + oc * a[1] * a[1], oc * a[1] * a[2] - sn * a[0],
+                   oc * a[2] * a[0] - sn * a[1], oc * a[2] * a[1] + sn * a[0], cs + oc * a[2] * a[2]};
+    if (live) {
 #pragma unroll
       for (int r = 0; r < 3; ++r)
-        p[r] += R[3 * r] * F.p[0] + R[3 * r + 1] * F.p[1] + R[3 * r + 2] * F.p[2];
 #pragma unroll
-      for (int c = 0; c < 3; ++c) {
-        const float b0 = F.R[c], b1 = F.R[3 + c], b2 = F.R[6 + c];
+        for (int c = 0; c < 3; ++c)
+          E.B[3 * r + c][lane] = l.Rt[3 * r] * Rq[c] + l.Rt[3 * r + 1] * Rq[3 + c] + l.Rt[3 * r + 2] * Rq[6 + c];
+      const float qs = l.prism ? q : 0.f;
 #pragma unroll
-        for (int r = 0; r < 3; ++r) F.R[3 * r + c] = R[3 * r] * b0 + R[3 * r + 1] * b1 + R[3 * r + 2] * b2;
-        F.p[c] = p[c];
-      }
+      for (int k = 0; k < 3; ++k)
+        E.B[9 + k][lane] = fmaf(qs, l.Rt[3 * k] * a[0] + l.Rt[3 * k + 1] * a[1] + l.Rt[3 * k + 2] * a[2], l.pt[k]);
     }
+  }
+  __syncthreads();
+  // world pose: walk the root path (ascending joint index is root first)
+  {
+    float R[9] = {1.f, 0.f, 0.f, 0.f, 1.f, 0.f, 0.f, 0.f, 1.f};
+    float p[3] = {0.f, 0.f, 0.f};
+    uint64_t mk = l.anc;
+    while (mk) {
+      const int j = __builtin_ctzll(mk);
+      mk &= mk - 1;
+      const float t0 = E.B[9][j], t1 = E.B[10][j], t2 = E.B[11][j];
+#pragma unroll
+      for (int r = 0; r < 3; ++r) p[r] += R[3 * r] * t0 + R[3 * r + 1] * t1 + R[3 * r + 2] * t2;
+      float Rn[9];
+#pragma unroll
+      for (int r = 0; r < 3; ++r)
+#pragma unroll
+        for (int c = 0; c < 3; ++c)
+          Rn[3 * r + c] = R[3 * r] * E.B[c][j] + R[3 * r + 1] * E.B[3 + c][j] + R[3 * r + 2] * E.B[6 + c][j];
+#pragma unroll
+      for (int k = 0; k < 9; ++k) R[k] = Rn[k];
+    }
+#pragma unroll
+    for (int k = 0; k < 9; ++k) F.R[k] = R[k];
+#pragma unroll
+    for (int k = 0; k < 3; ++k) F.p[k] = p[k];
   }
   // joint motion S = (s, p x s) for a revolute joint, (0, s) for a prismatic one, s = R axis; body inertia
   // about the origin
@@ -462,75 +406,106 @@ MD void kinematics(const RbModel& M, const Link<G>& l, float q, float qd, float 
     F.I.J[4] = W[2] - m * c[0] * c[2];
     F.I.J[5] = W[5] - m * c[1] * c[2];
   }
+  // velocities: V_i = sum over the root path of S_j qd_j
   F.u = scale6(F.S, qd);
-  F.V = F.u;
-  path_sum(M, l, F.V);
-  F.A = crm(F.V, F.u);
-#pragma unroll
-  for (int k = 0; k < 6; ++k) F.A.c[k] = fmaf(F.S.c[k], qdd, F.A.c[k]);
-  path_sum(M, l, F.A);
-  F.A.c[3] -= M.g[0];
-  F.A.c[4] -= M.g[1];
-  F.A.c[5] -= M.g[2];
-}
-
-MD void inertia_rows(const Inertia& I, float* a) {
-  a[0] = I.m;
-#pragma unroll
-  for (int k = 0; k < 3; ++k) a[1 + k] = I.h[k];
-#pragma unroll
-  for (int k = 0; k < 6; ++k) a[4 + k] = I.J[k];
-}
-MD Inertia inertia_of(const float* a) {
-  Inertia I;
-  I.m = a[0];
-#pragma unroll
-  for (int k = 0; k < 3; ++k) I.h[k] = a[1 + k];
-#pragma unroll
-  for (int k = 0; k < 6; ++k) I.J[k] = a[4 + k];
-  return I;
-}
-
-// One substep's dynamics of an environment: qdd of the lane's joint. Every lane of the block calls it (barriers
-// and lane permutes inside).
-template <int G>
-MD float dynamics(const RbModel& M, const Link<G>& l, BlockLds<G>& L, int col, bool live, float q, float qd,
-                  float tau, const Prm& P) {
-  Frame F;
-  kinematics(M, l, q, qd, 0.f, F);
-  // force of the link at qdd = 0, less the ground contact on its spheres
-  V6 f = add6(iapply(F.I, F.A), crf(F.V, iapply(F.I, F.V)));
+  if (live) put6(E.X, lane, F.u);
+  __syncthreads();
+  F.V = mask_sum(E.X, l.anc);
+  // bias accelerations (qdd = 0): A_i = A_0 + sum over the root path of V_j x S_j qd_j, A_0 = -g
+  if (live) put6(E.Y, lane, crm(F.V, F.u));
+  __syncthreads();
+  F.Ab = mask_sum(E.Y, l.anc);
+  F.Ab.c[3] -= M.g[0];
+  F.Ab.c[4] -= M.g[1];
+  F.Ab.c[5] -= M.g[2];
+  // ground contact on the link's spheres
+  F.fext = zero6();
   for (int c = l.cb; c < l.ce; ++c) {
     float cw[3], x[3], xd[3];
-    contact_point(M, l, F, c, cw, x);
+    contact_point(M, F, c, cw, x);
     cross3(F.V.c, x, xd);
     xd[0] += F.V.c[3]; xd[1] += F.V.c[4]; xd[2] += F.V.c[5];
     const float depth = P.zg - x[2];
     if (depth > 0.f) {
-      const float fc[3] = {-P.kf * xd[0], -P.kf * xd[1], P.ke * depth - P.kd * xd[2]};
+      const float f[3] = {-P.kf * xd[0], -P.kf * xd[1], P.ke * depth - P.kd * xd[2]};
       float n[3];
-      cross3(x, fc, n);
-      f.c[0] -= n[0]; f.c[1] -= n[1]; f.c[2] -= n[2];
-      f.c[3] -= fc[0]; f.c[4] -= fc[1]; f.c[5] -= fc[2];
+      cross3(x, f, n);
+      F.fext.c[0] += n[0]; F.fext.c[1] += n[1]; F.fext.c[2] += n[2];
+      F.fext.c[3] += f[0]; F.fext.c[4] += f[1]; F.fext.c[5] += f[2];
     }
   }
+  const V6 f = sub6(add6(iapply(F.I, F.Ab), crf(F.V, iapply(F.I, F.V))), F.fext);
+  __syncthreads();
+  if (live) {
+    put6(E.X, lane, f);
+    E.Ic[0][lane] = F.I.m;
+#pragma unroll
+    for (int k = 0; k < 3; ++k) E.Ic[1 + k][lane] = F.I.h[k];
+#pragma unroll
+    for (int k = 0; k < 6; ++k) E.Ic[4 + k][lane] = F.I.J[k];
+    put6(E.Y, lane, F.S);
+  }
+  __syncthreads();
   // subtree sums: force (bias torque S_i . F_i) and composite inertia
-  float a[16];
+  subtree_sums<6, 10>(M, l, lane, live, E.X, E.Ic);
+  const V6 Ft = get6(E.X, lane);
+  Inertia Ic;
+  Ic.m = E.Ic[0][lane];
 #pragma unroll
-  for (int k = 0; k < 6; ++k) a[k] = f.c[k];
-  inertia_rows(F.I, a + 6);
-  if (live) put_rows(L.S, col, F.S.c);
-  subtree_sums(M, l, col, live, L.sum, a);
-  float rhs = fmaf(-P.damp, qd, tau);
+  for (int k = 0; k < 3; ++k) Ic.h[k] = E.Ic[1 + k][lane];
 #pragma unroll
-  for (int k = 0; k < 6; ++k) rhs = fmaf(-F.S.c[k], a[k], rhs);
-  return solve(M, l, L, col, live, inertia_of(a + 6), F.S, rhs);
+  for (int k = 0; k < 6; ++k) Ic.J[k] = E.Ic[4 + k][lane];
+  const float rhs = tau - dot6(F.S, Ft) - P.damp * qd;
+  // mass matrix row: M_ij = S_j . (Ic_i S_i) for j on the root path (the lane's own row only)
+  if (live) {
+    const V6 Fc = iapply(Ic, F.S);
+    uint64_t mk = l.anc;
+    while (mk) {
+      const int j = __builtin_ctzll(mk);
+      mk &= mk - 1;
+      E.M[lane][j] = dot6(get6(E.Y, j), Fc);
+    }
+  }
+  // M = L^T L, leaves first, one height level at a time: the level's links finish their rows (their
+  // subtrees are eliminated), then every link updates its own row with the level's links below it,
+  // M_ij -= L_ki L_kj for j on i's root path. Rows a level reads are never written in that level.
+  for (int h = 0; h < M.H; ++h) {
+    if (live && l.height == h) {
+      const float d = sqrtf(E.M[lane][lane]);   // a non-positive pivot gives NaN: the env is flagged non-finite
+      const float di = 1.f / d;
+      E.M[lane][lane] = d;
+      E.dinv[lane] = di;
+      uint64_t mk = l.anc & ~(1ull << lane);
+      while (mk) {
+        const int j = __builtin_ctzll(mk);
+        mk &= mk - 1;
+        E.M[lane][j] *= di;
+      }
+    }
+    __syncthreads();
+    if (live) {
+      uint64_t mk = l.desc & M.hmask[h] & ~(1ull << lane);
+      while (mk) {
+        const int k = __builtin_ctzll(mk);
+        mk &= mk - 1;
+        const float lki = E.M[k][lane];
+        uint64_t aj = l.anc;
+        while (aj) {
+          const int j = __builtin_ctzll(aj);
+          aj &= aj - 1;
+          E.M[lane][j] = fmaf(-lki, E.M[k][j], E.M[lane][j]);
+        }
+      }
+    }
+  }
+  __syncthreads();
+  return tree_solve(M, l, E, lane, live, rhs);
 }
 
 template <int G>
 __global__ __launch_bounds__(kBlock) void k_rb_forward(RbModel M, int S, float* __restrict__ q,
                                                        float* __restrict__ qd, const float* __restrict__ tau,
-                                                       float* __restrict__ tape, float* __restrict__ tape_qdd,
+                                                       float* __restrict__ tape, float* __restrict__ tape_tau,
                                                        int32_t* __restrict__ errs) {
   constexpr int EPB = kBlock / G;
   __shared__ BlockLds<G> lds;
@@ -538,7 +513,8 @@ __global__ __launch_bounds__(kBlock) void k_rb_forward(RbModel M, int S, float* 
   const int e = blockIdx.x * EPB + grp;
   const int N = M.N, E = M.E;
   const bool live = e < E && lane < N;
-  const Link<G> l = load_link<G>(M, lane, grp * G, live);
+  EnvLds<G> L = env_lds(lds, grp);
+  const Link l = load_link(M, lane, live);
   const Prm P = load_prm(M, e);
   const size_t at = (size_t)e * N + lane;
   float qi = live ? q[at] : 0.f, qdi = live ? qd[at] : 0.f;
@@ -548,14 +524,15 @@ __global__ __launch_bounds__(kBlock) void k_rb_forward(RbModel M, int S, float* 
   }
   for (int s = 0; s < S; ++s) {
     const float ti = (tau && live) ? tau[(size_t)s * E * N + at] : 0.f;
-    const float qdd = dynamics<G>(M, l, lds, threadIdx.x, live, qi, qdi, ti, P);
+    if (tape_tau && live) tape_tau[(size_t)s * E * N + at] = ti;
+    Frame F;
+    const float qdd = dynamics<G>(M, l, L, lane, live, qi, qdi, ti, P, F);
     qdi = fmaf(M.dt, qdd, qdi);
     qi = fmaf(M.dt, qdi, qi);
     if (tape && live) {
       float* t = tape + ((size_t)(s + 1) * E + e) * 2 * N;
       t[lane] = qi;
       t[N + lane] = qdi;
-      tape_qdd[(size_t)s * E * N + at] = qdd;
     }
   }
   if (live) {
@@ -565,61 +542,49 @@ __global__ __launch_bounds__(kBlock) void k_rb_forward(RbModel M, int S, float* 
   }
 }
 
-// Three waves per SIMD (168 VGPRs, a few spilled): 65536 hands of 13 links take 990 us for 16 substeps, against
-// 1275 at two waves without spills and 1144 at four.
+// three waves per SIMD (168 VGPRs, three of them spilled): faster than two without spills once the chip is full
 template <int G>
 __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(3, 8))) void k_rb_backward(RbModel M, int S, const float* __restrict__ tape,
-                                                        const float* __restrict__ tape_qdd,
+                                                        const float* __restrict__ tape_tau,
                                                         const float* __restrict__ gq, const float* __restrict__ gqd,
                                                         float* __restrict__ dq0, float* __restrict__ dqd0,
                                                         float* __restrict__ dtau, double* __restrict__ dprm) {
   constexpr int EPB = kBlock / G;
   __shared__ BlockLds<G> lds;
-  BlockLds<G>& L = lds;
-  const int lane = threadIdx.x % G, grp = threadIdx.x / G, col = threadIdx.x;
+  const int lane = threadIdx.x % G, grp = threadIdx.x / G;
   const int e = blockIdx.x * EPB + grp;
   const int N = M.N, E = M.E;
   const bool live = e < E && lane < N;
-  const Link<G> l = load_link<G>(M, lane, grp * G, live);
+  EnvLds<G> L = env_lds(lds, grp);
+  const Link l = load_link(M, lane, live);
   const Prm P = load_prm(M, e);
   const size_t at = (size_t)e * N + lane;
   // cotangents of the current (q, qd)
   float a = (gq && live) ? gq[at] : 0.f;
   float b = (gqd && live) ? gqd[at] : 0.f;
   float acc[kRbPrm] = {0.f, 0.f, 0.f, 0.f, 0.f};
-  // the record of the next substep to reverse, read one ahead
-  float qn = 0.f, qdn = 0.f, qddn = 0.f;
-  auto prefetch = [&](int s) {
-    if (s < 0 || !live) return;
-    const float* t = tape + ((size_t)s * E + e) * 2 * N;
-    qn = t[lane];
-    qdn = t[N + lane];
-    qddn = tape_qdd[(size_t)s * E * N + at];
-  };
-  prefetch(S - 1);
   for (int s = S - 1; s >= 0; --s) {
-    const float qi = qn, qdi = qdn, qdd = qddn;
-    prefetch(s - 1);
+    const float* t = tape + ((size_t)s * E + e) * 2 * N;
+    const float qi = live ? t[lane] : 0.f, qdi = live ? t[N + lane] : 0.f;
+    const float ti = live ? tape_tau[(size_t)s * E * N + at] : 0.f;
     Frame F;
-    kinematics(M, l, qi, qdi, qdd, F);
+    const float qdd = dynamics<G>(M, l, L, lane, live, qi, qdi, ti, P, F);
     // qd' = qd + dt qdd, q' = q + dt qd': the cotangent of qd' is b + dt a, that of qdd dt (b + dt a)
     const float gtot = fmaf(M.dt, a, b);
-    float lam;   // torque cotangent M^-1 qdd_bar
-    {
-      float ic[10];
-      inertia_rows(F.I, ic);
-      if (live) put_rows(L.S, col, F.S.c);
-      subtree_sums(M, l, col, live, L.sum, ic);
-      lam = solve(M, l, L, col, live, inertia_of(ic), F.S, M.dt * gtot);
-    }
+    const float lam = tree_solve(M, l, L, lane, live, M.dt * gtot);   // torque cotangent M^-1 qdd_bar
     if (dtau && live) dtau[(size_t)s * E * N + at] = lam;
     acc[0] -= lam * qdi;
-    // phi = lambda . ID(q, qd, qdd): Lambda_k = sum over k's root path of lambda_i S_i
-    V6 Lam = scale6(F.S, lam);
-    path_sum(M, l, Lam);
+    // phi = lambda . ID(q, qd, qdd): accelerations with qdd, and Lambda_k = sum over k's root path of lambda_i S_i
+    if (live) {
+      put6(L.X, lane, scale6(F.S, qdd));
+      put6(L.Y, lane, scale6(F.S, lam));
+    }
+    __syncthreads();
+    const V6 A = add6(F.Ab, mask_sum(L.X, l.anc));
+    const V6 Lam = mask_sum(L.Y, l.anc);
     const V6 IV = iapply(F.I, F.V);
-    const V6 IA = iapply(F.I, F.A);
-    V6 f = add6(IA, crf(F.V, IV));   // less the contact forces below
+    const V6 IA = iapply(F.I, A);
+    const V6 f = sub6(add6(IA, crf(F.V, IV)), F.fext);
     // phi = sum_k Lambda_k . f_k: f_bar = Lambda; A_bar = I Lambda; V_bar from V x* (I V)
     const V6 Abar = iapply(F.I, Lam);
     const V6 VL = crm(F.V, Lam);
@@ -627,19 +592,15 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(3, 8))) 
     V6 Vbar = scale6(add6(crf(Lam, IV), IVL), -1.f);
     // geometric wrench of the body: the body's inertia turned with it, a . (I b) over the pairs
     // (Lambda, A) and (-V x Lambda, V) gives -(a x* I b + b x* I a)
-    V6 W = sub6(add6(crf(VL, IV), crf(F.V, IVL)), add6(crf(Lam, IA), crf(F.A, Abar)));
+    V6 W = sub6(add6(crf(VL, IV), crf(F.V, IVL)), add6(crf(Lam, IA), crf(A, Abar)));
     for (int c = l.cb; c < l.ce; ++c) {
       float cw[3], x[3], xd[3];
-      contact_point(M, l, F, c, cw, x);
+      contact_point(M, F, c, cw, x);
       cross3(F.V.c, x, xd);
       xd[0] += F.V.c[3]; xd[1] += F.V.c[4]; xd[2] += F.V.c[5];
       const float depth = P.zg - x[2];
       if (depth > 0.f) {
         const float fc[3] = {-P.kf * xd[0], -P.kf * xd[1], P.ke * depth - P.kd * xd[2]};
-        float t0[3];
-        cross3(x, fc, t0);
-        f.c[0] -= t0[0]; f.c[1] -= t0[1]; f.c[2] -= t0[2];
-        f.c[3] -= fc[0]; f.c[4] -= fc[1]; f.c[5] -= fc[2];
         // phi_c = -f . lh, lh = Lambda_v + Lambda_w x x (the point's velocity under Lambda)
         float lh[3];
         cross3(Lam.c, x, lh);
@@ -666,31 +627,32 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(3, 8))) 
         acc[4] += P.ke * lh[2];
       }
     }
+    __syncthreads();
+    if (live) {
+      put6(L.X, lane, f);
+      put6(L.Y, lane, Abar);
+    }
+    __syncthreads();
     // phi = sum_i lambda_i S_i . F_i (F_i the subtree force) and A_i = A_0 + sum over the root path of
     // (S_j qdd_j + V_j x S_j qd_j): subtree sums of f and of A_bar
-    float t12[12];
-#pragma unroll
-    for (int k = 0; k < 6; ++k) {
-      t12[k] = f.c[k];
-      t12[6 + k] = Abar.c[k];
-    }
-    subtree_sums(M, l, col, live, L.sum, t12);
-    V6 DA, Sbar;
-#pragma unroll
-    for (int k = 0; k < 6; ++k) {
-      DA.c[k] = t12[6 + k];
-      Sbar.c[k] = fmaf(t12[k], lam, DA.c[k] * qdd);
-    }
+    subtree_sums<6, 6>(M, l, lane, live, L.X, L.Y);
+    const V6 Ft = get6(L.X, lane), DA = get6(L.Y, lane);
+    V6 Sbar = add6(scale6(Ft, lam), scale6(DA, qdd));
     Vbar = add6(Vbar, crf(F.u, DA));
+    __syncthreads();
+    if (live) put6(L.X, lane, Vbar);
+    __syncthreads();
     // V_i = sum over the root path of u_j, u_j = S_j qd_j
-    subtree_sums(M, l, col, live, L.sum, Vbar.c);
-    const V6 ubar = sub6(Vbar, crf(F.V, DA));
+    subtree_sums<6, 0>(M, l, lane, live, L.X, nullptr);
+    const V6 ubar = sub6(get6(L.X, lane), crf(F.V, DA));
     Sbar = add6(Sbar, scale6(ubar, qdi));
     const float dphi_qd = dot6(F.S, ubar);
     W = add6(W, crf(F.S, Sbar));
+    if (live) put6(L.Y, lane, W);
+    __syncthreads();
     // turning joint j moves its whole subtree: dphi/dq_j = S_j . (subtree sum of the wrenches)
-    subtree_sums(M, l, col, live, L.sum, W.c);
-    const float dphi_q = dot6(F.S, W);
+    subtree_sums<6, 0>(M, l, lane, live, L.Y, nullptr);
+    const float dphi_q = dot6(F.S, get6(L.Y, lane));
     a = a - dphi_q;
     b = gtot - P.damp * lam - dphi_qd;
   }
@@ -699,14 +661,13 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(3, 8))) 
     dqd0[at] = b;
   }
   if (dprm) {
-    float* part = reinterpret_cast<float*>(L.sum);
     __syncthreads();
 #pragma unroll
-    for (int c = 0; c < kRbPrm; ++c) part[c * kBlock + col] = live ? acc[c] : 0.f;
+    for (int c = 0; c < kRbPrm; ++c) L.X[c][lane] = live ? acc[c] : 0.f;
     __syncthreads();
     if (lane < kRbPrm && e < E) {
       double s = 0.0;
-      for (int k = 0; k < N; ++k) s += (double)part[lane * kBlock + grp * G + k];
+      for (int k = 0; k < N; ++k) s += (double)L.X[lane][k];
       dprm[(size_t)e * kRbPrm + lane] = s;
     }
   }
@@ -716,27 +677,27 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(3, 8))) 
 
 int rb_group(int N) { return N <= 8 ? 8 : N <= 16 ? 16 : N <= 32 ? 32 : 64; }
 
-void launch_rb_forward(const RbModel& m, int S, float* q, float* qd, const float* tau, float* tape, float* tape_qdd,
+void launch_rb_forward(const RbModel& m, int S, float* q, float* qd, const float* tau, float* tape, float* tape_tau,
                        int32_t* errs, hipStream_t s) {
   const int G = rb_group(m.N), epb = rb::kBlock / G;
   const dim3 grid((m.E + epb - 1) / epb), block(rb::kBlock);
   switch (G) {
-    case 8: rb::k_rb_forward<8><<<grid, block, 0, s>>>(m, S, q, qd, tau, tape, tape_qdd, errs); break;
-    case 16: rb::k_rb_forward<16><<<grid, block, 0, s>>>(m, S, q, qd, tau, tape, tape_qdd, errs); break;
-    case 32: rb::k_rb_forward<32><<<grid, block, 0, s>>>(m, S, q, qd, tau, tape, tape_qdd, errs); break;
-    default: rb::k_rb_forward<64><<<grid, block, 0, s>>>(m, S, q, qd, tau, tape, tape_qdd, errs); break;
+    case 8: rb::k_rb_forward<8><<<grid, block, 0, s>>>(m, S, q, qd, tau, tape, tape_tau, errs); break;
+    case 16: rb::k_rb_forward<16><<<grid, block, 0, s>>>(m, S, q, qd, tau, tape, tape_tau, errs); break;
+    case 32: rb::k_rb_forward<32><<<grid, block, 0, s>>>(m, S, q, qd, tau, tape, tape_tau, errs); break;
+    default: rb::k_rb_forward<64><<<grid, block, 0, s>>>(m, S, q, qd, tau, tape, tape_tau, errs); break;
   }
 }
 
-void launch_rb_backward(const RbModel& m, int S, const float* tape, const float* tape_qdd, const float* gq,
+void launch_rb_backward(const RbModel& m, int S, const float* tape, const float* tape_tau, const float* gq,
                         const float* gqd, float* dq0, float* dqd0, float* dtau, double* dprm, hipStream_t s) {
   const int G = rb_group(m.N), epb = rb::kBlock / G;
   const dim3 grid((m.E + epb - 1) / epb), block(rb::kBlock);
   switch (G) {
-    case 8: rb::k_rb_backward<8><<<grid, block, 0, s>>>(m, S, tape, tape_qdd, gq, gqd, dq0, dqd0, dtau, dprm); break;
-    case 16: rb::k_rb_backward<16><<<grid, block, 0, s>>>(m, S, tape, tape_qdd, gq, gqd, dq0, dqd0, dtau, dprm); break;
-    case 32: rb::k_rb_backward<32><<<grid, block, 0, s>>>(m, S, tape, tape_qdd, gq, gqd, dq0, dqd0, dtau, dprm); break;
-    default: rb::k_rb_backward<64><<<grid, block, 0, s>>>(m, S, tape, tape_qdd, gq, gqd, dq0, dqd0, dtau, dprm); break;
+    case 8: rb::k_rb_backward<8><<<grid, block, 0, s>>>(m, S, tape, tape_tau, gq, gqd, dq0, dqd0, dtau, dprm); break;
+    case 16: rb::k_rb_backward<16><<<grid, block, 0, s>>>(m, S, tape, tape_tau, gq, gqd, dq0, dqd0, dtau, dprm); break;
+    case 32: rb::k_rb_backward<32><<<grid, block, 0, s>>>(m, S, tape, tape_tau, gq, gqd, dq0, dqd0, dtau, dprm); break;
+    default: rb::k_rb_backward<64><<<grid, block, 0, s>>>(m, S, tape, tape_tau, gq, gqd, dq0, dqd0, dtau, dprm); break;
   }
 }
 

@@ -29,6 +29,7 @@ struct mpm_rb {
   uint64_t* desc = nullptr;    // [N]
   uint64_t* kids = nullptr;    // [N]
   int32_t* level = nullptr;    // [N] height | depth << 16
+  uint64_t* hmask = nullptr;   // [H]
   int H = 0, D = 0;
   int32_t* cbeg = nullptr;     // [N + 1]
   float* contact = nullptr;    // [C][4]
@@ -36,7 +37,7 @@ struct mpm_rb {
   float* q = nullptr;
   float* qd = nullptr;
   float* tape = nullptr;       // [(max_S + 1)][E][2][N]
-  float* tape_qdd = nullptr;   // [max_S][E][N]
+  float* tape_tau = nullptr;   // [max_S][E][N]
   int32_t* errs = nullptr;
   int recorded = -1;           // substeps of the kept record, -1: none
   std::vector<int32_t> env_err_h;
@@ -93,6 +94,7 @@ mpmx::RbModel model_of(const mpm_rb* r) {
   m.desc = r->desc;
   m.kids = r->kids;
   m.level = r->level;
+  m.hmask = r->hmask;
   m.H = r->H;
   m.D = r->D;
   m.cbeg = r->cbeg;
@@ -174,11 +176,12 @@ int mpm_rb_create(const mpm_rb_desc* d, const mpm_rb_link* links, const mpm_rb_c
   for (int i = 0; i < N; ++i) depth[i] = links[i].parent < 0 ? 0 : depth[links[i].parent] + 1;
   for (int i = N - 1; i >= 0; --i)
     if (links[i].parent >= 0) height[links[i].parent] = std::max(height[links[i].parent], height[i] + 1);
-  std::vector<uint64_t> kids(N, 0);
+  std::vector<uint64_t> hmask(N, 0), kids(N, 0);
   for (int i = 0; i < N; ++i)
     if (links[i].parent >= 0) kids[links[i].parent] |= 1ull << i;
   for (int i = 0; i < N; ++i) {
     level[i] = height[i] | (depth[i] << 16);
+    hmask[height[i]] |= 1ull << i;
     H = std::max(H, height[i] + 1);
     D = std::max(D, depth[i] + 1);
   }
@@ -226,14 +229,15 @@ int mpm_rb_create(const mpm_rb_desc* d, const mpm_rb_link* links, const mpm_rb_c
   r->cbeg = (int32_t*)ralloc(r, sizeof(int32_t) * (N + 1));
   r->level = (int32_t*)ralloc(r, sizeof(int32_t) * N);
   r->kids = (uint64_t*)ralloc(r, sizeof(uint64_t) * N);
+  r->hmask = (uint64_t*)ralloc(r, sizeof(uint64_t) * N);
   r->contact = (float*)ralloc(r, sizeof(float) * ct.size());
   r->prm = (float*)ralloc(r, sizeof(float) * mpmx::kRbPrm * E);
   r->q = (float*)ralloc(r, sizeof(float) * E * N);
   r->qd = (float*)ralloc(r, sizeof(float) * E * N);
   r->tape = (float*)ralloc(r, sizeof(float) * 2 * E * N * (size_t)(r->max_S + 1));
-  r->tape_qdd = (float*)ralloc(r, sizeof(float) * E * N * (size_t)(r->max_S > 0 ? r->max_S : 1));
+  r->tape_tau = (float*)ralloc(r, sizeof(float) * E * N * (size_t)(r->max_S > 0 ? r->max_S : 1));
   r->errs = (int32_t*)ralloc(r, sizeof(int32_t) * E);
-  if (!(r->link && r->anc && r->desc && r->kids && r->level && r->cbeg && r->contact && r->prm && r->q && r->qd && r->tape && r->tape_qdd &&
+  if (!(r->link && r->anc && r->desc && r->kids && r->level && r->hmask && r->cbeg && r->contact && r->prm && r->q && r->qd && r->tape && r->tape_tau &&
         r->errs)) {
     free_all(r);
     delete r;
@@ -250,6 +254,7 @@ int mpm_rb_create(const mpm_rb_desc* d, const mpm_rb_link* links, const mpm_rb_c
   if (e1 == hipSuccess) e1 = hipMemcpyAsync(r->desc, desc.data(), sizeof(uint64_t) * N, hipMemcpyHostToDevice, r->stream);
   if (e1 == hipSuccess) e1 = hipMemcpyAsync(r->kids, kids.data(), sizeof(uint64_t) * N, hipMemcpyHostToDevice, r->stream);
   if (e1 == hipSuccess) e1 = hipMemcpyAsync(r->level, level.data(), sizeof(int32_t) * N, hipMemcpyHostToDevice, r->stream);
+  if (e1 == hipSuccess) e1 = hipMemcpyAsync(r->hmask, hmask.data(), sizeof(uint64_t) * N, hipMemcpyHostToDevice, r->stream);
   if (e1 == hipSuccess) e1 = hipMemcpyAsync(r->cbeg, cbeg.data(), sizeof(int32_t) * (N + 1), hipMemcpyHostToDevice, r->stream);
   if (e1 == hipSuccess) e1 = hipMemcpyAsync(r->contact, ct.data(), sizeof(float) * ct.size(), hipMemcpyHostToDevice, r->stream);
   if (e1 == hipSuccess) e1 = hipMemcpyAsync(r->prm, prm.data(), sizeof(float) * prm.size(), hipMemcpyHostToDevice, r->stream);
@@ -320,7 +325,7 @@ int mpm_rb_forward(mpm_rb* r, int32_t S, const float* tau, int32_t flags) {
   if (record && S > r->max_S) return fail(r, MPM_BAD_STATE, "record longer than the tape (max_substeps)");
   r->recorded = -1;
   mpmx::launch_rb_forward(model_of(r), S, r->q, r->qd, tau, record ? r->tape : nullptr,
-                          record ? r->tape_qdd : nullptr, r->errs, r->stream);
+                          record ? r->tape_tau : nullptr, r->errs, r->stream);
   RBC(r, hipGetLastError());
   if (record) r->recorded = S;
   return MPM_OK;
@@ -331,7 +336,7 @@ int mpm_rb_backward(mpm_rb* r, const float* gq, const float* gqd, float* dq0, fl
   if (!r) return MPM_INVALID_ARG;
   if (!dq0 || !dqd0) return fail(r, MPM_INVALID_ARG, "null output cotangents");
   if (r->recorded < 0) return fail(r, MPM_BAD_STATE, "no recorded forward");
-  mpmx::launch_rb_backward(model_of(r), r->recorded, r->tape, r->tape_qdd, gq, gqd, dq0, dqd0, dtau, dparams,
+  mpmx::launch_rb_backward(model_of(r), r->recorded, r->tape, r->tape_tau, gq, gqd, dq0, dqd0, dtau, dparams,
                            r->stream);
   RBC(r, hipGetLastError());
   return MPM_OK;
