@@ -22,6 +22,22 @@
 //     of one (x, y) offset each: within a phase no two threads share a node, so
 //     plain 128-bit reads and writes do;
 //  5. each box node goes to the grid once, four lanes per node.
+//
+// Measured, us per launch, on 3.2 M water particles (16 envs, 96^3, 0.9 per cell), 640,000
+// corotated (32 envs, 48^3, 8 per cell) and 320,000 von Mises (128 envs, 48^3, 8 per
+// cell); before: a scatter per box node or per cell, with LDS copies of the grid
+// for the gathers, over a grid stored one channel at a time:
+//                 water          corotated      von Mises
+//   P2G           353 -> 240     63 -> 52       53 -> 35
+//   G2P           222 -> 126     25 -> 22.5     20 -> 19
+//   G2P + P2G     462 -> 289     71 -> 61       63 -> 46
+//   G2P adjoint   514 -> 344     71 -> 60       68 -> 50
+//   P2G adjoint   326 -> 195     65 -> 44       50 -> 35
+//   adjoint pair  749 -> 441     114 -> 89      100 -> 75
+// What bounds them now: at 8 per cell instruction issue (the vector ALUs are busy 67%
+// of a G2P + P2G and 75% of a pair, the rest is the scatter's chain of barriers); at
+// one per cell the box flush, 2.75 million 64-byte lines of global atomics per
+// launch at the chip's 20 per ns, 137 us, which the rest overlaps in part.
 #include "mpm_kernels.h"
 
 namespace mpmx {
@@ -35,10 +51,10 @@ constexpr int kBins = 8;           // task lengths told apart
 // larger pair leaves four blocks per CU (LDS) and holds a box of 28 z nodes
 // across a whole tile row. The smaller one with its 96 VGPRs leaves five
 // (32,000 bytes of LDS is the most for that): the scatter's barriers and
-// LDS chains want the fifth where the boxes fit. G2P2G, 2 M elastic particles
-// (256 envs, 6 per cell) 65.8 -> 60.9 us, 1 M von Mises (4 envs, 8 per cell) 53 ->
-// 46; where they do not, at 1.3 particles per cell, the second pass costs
-// more: 8 M water particles 289 -> 298. (384 nodes with six blocks lost to
+// LDS chains want the fifth where the boxes fit. G2P2G, 640,000 corotated particles
+// (32 envs, 48^3, 8 per cell) 65.8 -> 60.9 us, 320,000 von Mises (128 envs, 48^3, 8 per cell)
+// 53 -> 46; where they do not, at one particle per cell, the second pass costs
+// more: 3.2 M water particles (16 envs, 96^3) 289 -> 298. (384 nodes with six blocks lost to
 // one of the two at each of these.) The autotuner measures both.
 constexpr int kBoxLarge = 1024;
 constexpr int kBoxSmall = 640;
@@ -804,7 +820,7 @@ MD void g2p_adjoint_body(const EnvDev& e, int mat, bool valid, uint32_t t, const
 }
 
 // ----------------------------------------------------------------------------
-// kernels: one block per work item. MAT < 0 reads the material at run time.
+// kernels: one block per work item (figures: top of this file). MAT < 0 reads the material at run time.
 // An env past its substep count (k_call >= nsub) is frozen: its state and
 // cotangent pass through.
 // ----------------------------------------------------------------------------
@@ -829,6 +845,9 @@ __global__ void __launch_bounds__(256, waves_per_simd<BOXN>()) k_p2g_col(const f
   }, grid, flags, errs + it.env, S);
 }
 
+// G2P: 27 128-bit node reads per particle straight from the grid. Neighbouring
+// lanes read the same lines, which the L1 serves: staging boxes in LDS first took
+// 222 us where this takes 126 (3.2 M water particles; 3.7 TB/s of state alone).
 template <int MAT>
 __global__ void __launch_bounds__(256) k_g2p(const float* __restrict__ st, float* __restrict__ out, int64_t N,
                                              const EnvDev* __restrict__ envs, const WorkItem* __restrict__ items,
@@ -892,6 +911,9 @@ __global__ void __launch_bounds__(256, waves_per_simd<BOXN>()) k_g2p2g_col(const
   }, grid_out, flags_out, errs + it.env, S);
 }
 
+// G2P adjoint. Its gather of v and its payload share the particle's registers, so
+// the corotated and von Mises forms spill a little at five blocks per CU and are
+// still faster there (67 -> 60 us, 640,000 corotated particles).
 template <int BOXN, int MAT>
 __global__ void __launch_bounds__(256, waves_per_simd<BOXN>()) k_g2p_adjoint_col(const float* __restrict__ st,
                                                          const float* __restrict__ st_next,
@@ -916,6 +938,9 @@ __global__ void __launch_bounds__(256, waves_per_simd<BOXN>()) k_g2p_adjoint_col
   block_reduce_params(pb, pacc + (int64_t)it.env * 8);
 }
 
+// P2G adjoint: a gather of (mbar, Pbar) and the stress VJP; issue-bound. Four waves per
+// SIMD; the nodes are summed flat per (x, y) column, since sums nested per axis keep
+// more registers live and spill (640,000 corotated particles: 54 us nested, 44 flat).
 template <int MAT>
 __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4, 8)))
 k_p2g_adjoint(const float* __restrict__ st, const float* __restrict__ part, float* __restrict__ cot_out, int64_t N,
