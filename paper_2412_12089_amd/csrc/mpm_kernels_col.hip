@@ -49,13 +49,14 @@ constexpr int kBins = 8;           // task lengths told apart
 // Box budgets in nodes (a block with more takes several passes over slabs of z)
 // and room for base cells (a block with more adds to the grid directly). The
 // larger pair leaves four blocks per CU (LDS) and holds a box of 28 z nodes
-// across a whole tile row. The smaller one with its 96 VGPRs leaves five
-// (32,000 bytes of LDS is the most for that): the scatter's barriers and
-// LDS chains want the fifth where the boxes fit. G2P2G, 640,000 corotated particles
-// (32 envs, 48^3, 8 per cell) 65.8 -> 60.9 us, 320,000 von Mises (128 envs, 48^3, 8 per cell)
-// 53 -> 46; where they do not, at one particle per cell, the second pass costs
-// more: 3.2 M water particles (16 envs, 96^3) 289 -> 298. (384 nodes with six blocks lost to
-// one of the two at each of these.) The autotuner measures both.
+// across a whole tile row. The smaller one with its 96 VGPRs leaves five (32,000
+// bytes of LDS is the most for that): the scatter's barriers and LDS chains want
+// the fifth where the boxes fit. G2P + P2G, 640,000 corotated particles (32
+// envs, 48^3, 8 per cell) 65.8 -> 60.9 us, 320,000 von Mises (128 envs, 48^3, 8
+// per cell) 53 -> 46; where they do not, at one particle per cell, the second
+// pass costs more: 3.2 M water particles (16 envs, 96^3) 289 -> 298. (384 nodes
+// with six blocks lost to one of the two at each of these.) The autotuner
+// measures both.
 constexpr int kBoxLarge = 1024;
 constexpr int kBoxSmall = 640;
 template <int BOXN>
@@ -84,9 +85,9 @@ MD int wave_pk_min(int x) {
   return __builtin_amdgcn_readlane(x, 63);
 }
 
-// the block's runs (distinct tile rows): boxes of nodes, base cells
-// and (base column, z node) tasks, each concatenated over the runs. A run lies in one tile row, so it has at most 4 x
-// 4 columns of base cells and 6 x 6 of nodes.
+// the block's runs (distinct tile rows): boxes of nodes, base cells and (base
+// column, z node) tasks, each concatenated over the runs. A run lies in one tile
+// row, so it has at most 4 x 4 columns of base cells and 6 x 6 of nodes.
 struct Runs {
   int last[4], wsum[4];               // per wave: its last particle's tile row; row changes in it
   int rows[4][kWaveRows];             // per wave: the tile row after each change
@@ -186,9 +187,10 @@ MD void block_reduce_params(float pb[PB_COUNT], double* __restrict__ acc) {
 // the column scatter
 // ----------------------------------------------------------------------------
 // Runs, boxes and the counting sort for the block's particles with stencil
-// bases b (every thread calls it): pos = this thread's sorted position. False, for every thread, if the block's particles lie in more than
-// kMaxRuns tile rows or their boxes hold more base cells than there is room for
-// (the caller then adds to the grid directly).
+// bases b (every thread calls it): pos = this thread's sorted position. False,
+// for every thread, if the block's particles lie in more than kMaxRuns tile
+// rows or their boxes hold more base cells than there is room for (the caller
+// then adds to the grid directly).
 template <int BOXN>
 MD bool col_index(const EnvDev& e, const int b[3], bool valid, ColShared<BOXN>& S, int& pos) {
   const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
@@ -825,10 +827,10 @@ MD void g2p_adjoint_body(const EnvDev& e, int mat, bool valid, uint32_t t, const
 // cotangent pass through.
 // ----------------------------------------------------------------------------
 template <int BOXN, int MAT>
-__global__ void __launch_bounds__(256, waves_per_simd<BOXN>()) k_p2g_col(const float* __restrict__ st, int64_t N,
-                                                 const EnvDev* __restrict__ envs, const WorkItem* __restrict__ items,
-                                                 float* __restrict__ grid, uint32_t* __restrict__ flags,
-                                                 int32_t* __restrict__ errs, int k_call) {
+__global__ void __launch_bounds__(256, waves_per_simd<BOXN>())
+k_p2g_col(const float* __restrict__ st, int64_t N, const EnvDev* __restrict__ envs,
+          const WorkItem* __restrict__ items, float* __restrict__ grid, uint32_t* __restrict__ flags,
+          int32_t* __restrict__ errs, int k_call) {
   __shared__ ColShared<BOXN> S;
   const WorkItem it = items[blockIdx.x];
   const EnvDev& e = envs[it.env];
@@ -875,12 +877,10 @@ __global__ void __launch_bounds__(256) k_g2p(const float* __restrict__ st, float
 // tape once and is scattered from registers. k_call is substep k's call index;
 // an env frozen at k copies its state, one frozen at k + 1 only takes the G2P.
 template <int BOXN, int MAT>
-__global__ void __launch_bounds__(256, waves_per_simd<BOXN>()) k_g2p2g_col(const float* __restrict__ st, float* __restrict__ out, int64_t N,
-                                                   const EnvDev* __restrict__ envs,
-                                                   const WorkItem* __restrict__ items,
-                                                   const float* __restrict__ grid_in, float* __restrict__ grid_out,
-                                                   uint32_t* __restrict__ flags_out, int32_t* __restrict__ errs,
-                                                   int k_call) {
+__global__ void __launch_bounds__(256, waves_per_simd<BOXN>())
+k_g2p2g_col(const float* __restrict__ st, float* __restrict__ out, int64_t N, const EnvDev* __restrict__ envs,
+            const WorkItem* __restrict__ items, const float* __restrict__ grid_in, float* __restrict__ grid_out,
+            uint32_t* __restrict__ flags_out, int32_t* __restrict__ errs, int k_call) {
   __shared__ ColShared<BOXN> S;
   const WorkItem it = items[blockIdx.x];
   const EnvDev& e = envs[it.env];
@@ -915,13 +915,12 @@ __global__ void __launch_bounds__(256, waves_per_simd<BOXN>()) k_g2p2g_col(const
 // the corotated and von Mises forms spill a little at five blocks per CU and are
 // still faster there (67 -> 60 us, 640,000 corotated particles).
 template <int BOXN, int MAT>
-__global__ void __launch_bounds__(256, waves_per_simd<BOXN>()) k_g2p_adjoint_col(const float* __restrict__ st,
-                                                         const float* __restrict__ st_next,
-                                                         const float* __restrict__ cot, float* __restrict__ part,
-                                                         int64_t N, const EnvDev* __restrict__ envs,
-                                                         const WorkItem* __restrict__ items,
-                                                         const float* __restrict__ grid, float* __restrict__ gcot,
-                                                         double* __restrict__ pacc, int k_call) {
+__global__ void __launch_bounds__(256, waves_per_simd<BOXN>())
+k_g2p_adjoint_col(const float* __restrict__ st, const float* __restrict__ st_next,
+                  const float* __restrict__ cot, float* __restrict__ part, int64_t N,
+                  const EnvDev* __restrict__ envs, const WorkItem* __restrict__ items,
+                  const float* __restrict__ grid, float* __restrict__ gcot, double* __restrict__ pacc,
+                  int k_call) {
   __shared__ ColShared<BOXN> S;
   const WorkItem it = items[blockIdx.x];
   const EnvDev& e = envs[it.env];
