@@ -239,7 +239,7 @@ MD bool col_index(const EnvDev& e, const int b[3], bool valid, ColShared<BOXN>& 
       cols |= __ballot(mine && (b[0] & 3) == j) != 0ull ? 1 << j : 0;
       cols |= __ballot(mine && (b[1] & 3) == j) != 0ull ? 16 << j : 0;
     }
-    const int z = wave_pk_min(mine ? (b[2] & 0xffff) | (-b[2] << 16) : 0x7fff7fff);
+    const int z = wave_pk_min(mine ? (b[2] & 0xffff) | (int)((uint32_t)-b[2] << 16) : 0x7fff7fff);
     const int first_of_k = __ffsll((unsigned long long)of_k) - 1;
     const int tx = __builtin_amdgcn_readlane(b[0], first_of_k) & ~3, ty = __builtin_amdgcn_readlane(b[1], first_of_k) & ~3;
     if (lane == 0) {
@@ -399,7 +399,10 @@ MD void col_scatter(const EnvDev& e, ColShared<BOXN>& S, float mass, float* __re
     int longer = 0;
     const int mine = lane < kBins ? R.bin[lane] : 0;
 #pragma unroll
-    for (int k = kBins - 1; k > 0; --k) longer += lane < k ? __builtin_amdgcn_readlane(mine, k) : 0;
+    for (int k = kBins - 1; k > 0; --k) {
+      const int of_k = __builtin_amdgcn_readlane(mine, k);   // by every lane: the lane read may not be masked off
+      longer += lane < k ? of_k : 0;
+    }
     const int tasks = __builtin_amdgcn_readlane(longer + mine, 0);
 #pragma unroll
     for (int m = 0; m < kMine; ++m) {
