@@ -17,6 +17,7 @@
 namespace mpmx {
 
 #define MD __device__ __forceinline__
+#define MHD __host__ __device__ __forceinline__
 
 enum : int { MAT_NEOHOOKEAN = 0, MAT_COROTATED = 1, MAT_VONMISES = 2, MAT_FLUID_TAIT = 3, MAT_FLUID_PAPER = 4, MAT_COUNT = 5 };
 enum : int { ERR_NONFINITE = 1, ERR_OUT_OF_DOMAIN = 2 };
@@ -267,7 +268,7 @@ MD Stencil make_stencil(const float x[3], int n, float fn) {
 // group 0 (m, P), group 1 (v, unused). Grid cotangent: group 0 (vbar, unused),
 // group 1 (mbar, Pbar).
 // Offset (in floats) of node (i, j, k)'s group 0:
-MD int64_t node_base(const EnvDev& e, int i, int j, int k) {
+MHD int64_t node_base(const EnvDev& e, int i, int j, int k) {
   const int tile = ((i >> 2) * e.T + (j >> 2)) * e.T + (k >> 2);
   const int local = ((i & 3) << 4) | ((j & 3) << 2) | (k & 3);
   return (e.tile_off + tile) * 512 + local * 4;
@@ -277,25 +278,30 @@ constexpr int G1 = 256;  // group 1 relative to group 0
 MD float4 ld4(const float* p) { return *reinterpret_cast<const float4*>(p); }
 MD void st4(float* p, float a, float b, float c, float d) { *reinterpret_cast<float4*>(p) = make_float4(a, b, c, d); }
 
-// node_base is separable per axis: node_base(e, i, j, k) = e.tile_off * 512 +
-// ax(i) + ay(j) + az(k). A gather precomputes the three offsets of each axis
-// for its stencil once (element offsets within the env's grid block, below
-// 2^32 for any grid this library allocates) and then addresses each of the 27
-// nodes with two additions.
+// node_base is separable per axis: node_base(e, i, j, k) / 4 = e.tile_off * 128 +
+// ax(i) + ay(j) + az(k), counted in groups of four floats. A gather precomputes
+// the three offsets of each axis for its stencil once and then addresses each of
+// the 27 nodes with two 32-bit additions. The offsets lie within the env's grid
+// block, T^3 * 128 groups: at most 2^31 for the largest grid a batch takes (1024
+// nodes per axis, T = 256). Counted in floats they would pass 2^32 from T = 204 on.
 struct StencilAddr {
   uint32_t x[3], y[3], z[3];
 };
-MD StencilAddr stencil_addr(const EnvDev& e, const int b[3]) {
+MHD StencilAddr stencil_addr(const EnvDev& e, const int b[3]) {
   StencilAddr s;
   const uint32_t T = (uint32_t)e.T;
 #pragma unroll
   for (int o = 0; o < 3; ++o) {
     const uint32_t i = (uint32_t)(b[0] + o), j = (uint32_t)(b[1] + o), k = (uint32_t)(b[2] + o);
-    s.x[o] = (i >> 2) * T * T * 512u + ((i & 3u) << 6);
-    s.y[o] = (j >> 2) * T * 512u + ((j & 3u) << 4);
-    s.z[o] = (k >> 2) * 512u + ((k & 3u) << 2);
+    s.x[o] = (i >> 2) * T * T * 128u + ((i & 3u) << 4);
+    s.y[o] = (j >> 2) * T * 128u + ((j & 3u) << 2);
+    s.z[o] = (k >> 2) * 128u + (k & 3u);
   }
   return s;
+}
+// group 1 of the env's nodes, addressed by those offsets
+MHD const float4* env_group1(const EnvDev& e, const float* grid) {
+  return reinterpret_cast<const float4*>(grid + e.tile_off * 512 + G1);
 }
 
 // --------------------------------------------------------------------------

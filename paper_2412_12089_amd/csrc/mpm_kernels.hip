@@ -893,7 +893,7 @@ __global__ void __launch_bounds__(256) k_g2p_direct(const float* __restrict__ st
   float vn[3] = {0.f, 0.f, 0.f};
   M3 Cn = m3_zero();
   const StencilAddr sa = stencil_addr(e, sc.b);
-  const float* genv = grid + (int64_t)e.tile_off * 512;
+  const float4* genv = env_group1(e, grid);
   float wdz[3];
   for (int o = 0; o < 3; ++o) wdz[o] = sc.w[2][o] * ((float)o - sc.f[2]) * e.dx;
 #pragma unroll
@@ -907,7 +907,7 @@ __global__ void __launch_bounds__(256) k_g2p_direct(const float* __restrict__ st
       float col[3] = {0.f, 0.f, 0.f}, colz[3] = {0.f, 0.f, 0.f};
 #pragma unroll
       for (int oz = 0; oz < 3; ++oz) {
-        const float4 v4 = ld4(genv + (sa.x[ox] + sa.y[oy] + sa.z[oz]) + G1);
+        const float4 v4 = genv[sa.x[ox] + sa.y[oy] + sa.z[oz]];
         const float vi[3] = {v4.x, v4.y, v4.z};
         const float W = wxy * sc.w[2][oz], Wd = wxy * wdz[oz];
 #pragma unroll

@@ -542,7 +542,7 @@ MD void direct_scatter(const EnvDev& e, const Stencil& sc, const float g[3], con
 MD void gather_v_nested(const EnvDev& e, const float* __restrict__ grid, const float x[3], float vn[3], M3& Cn) {
   const Stencil sc = make_stencil(x, e.n, e.fn);
   const StencilAddr sa = stencil_addr(e, sc.b);
-  const float* genv = grid + (int64_t)e.tile_off * 512 + G1;
+  const float4* genv = env_group1(e, grid);
   Cn = m3_zero();
   vn[0] = vn[1] = vn[2] = 0.f;
   float wdz[3], wdy[3];
@@ -559,7 +559,7 @@ MD void gather_v_nested(const EnvDev& e, const float* __restrict__ grid, const f
       float col[3] = {0.f, 0.f, 0.f}, colz[3] = {0.f, 0.f, 0.f};
 #pragma unroll
       for (int oz = 0; oz < 3; ++oz) {
-        const float4 v4 = ld4(genv + (ax + sa.y[oy] + sa.z[oz]));
+        const float4 v4 = genv[ax + sa.y[oy] + sa.z[oz]];
         const float vi[3] = {v4.x, v4.y, v4.z};
 #pragma unroll
         for (int a = 0; a < 3; ++a) {
@@ -600,7 +600,7 @@ MD void gather_v_nested(const EnvDev& e, const float* __restrict__ grid, const f
 MD void gather_v_flat(const EnvDev& e, const float* __restrict__ grid, const float x[3], float vn[3], M3& Cn) {
   const Stencil sc = make_stencil(x, e.n, e.fn);
   const StencilAddr sa = stencil_addr(e, sc.b);
-  const float* genv = grid + (int64_t)e.tile_off * 512 + G1;
+  const float4* genv = env_group1(e, grid);
   Cn = m3_zero();
   vn[0] = vn[1] = vn[2] = 0.f;
   float wdz[3];
@@ -615,7 +615,7 @@ MD void gather_v_flat(const EnvDev& e, const float* __restrict__ grid, const flo
       float col[3] = {0.f, 0.f, 0.f}, colz[3] = {0.f, 0.f, 0.f};   // sums of W v, W v d_z over the column
 #pragma unroll
       for (int oz = 0; oz < 3; ++oz) {
-        const float4 v4 = ld4(genv + (ax + sa.y[oy] + sa.z[oz]));
+        const float4 v4 = genv[ax + sa.y[oy] + sa.z[oz]];
         const float vi[3] = {v4.x, v4.y, v4.z};
         const float W = wxy * sc.w[2][oz], Wd = wxy * wdz[oz];
 #pragma unroll
@@ -704,7 +704,7 @@ MD void p2g_adjoint_particle(const EnvDev& e, int mat, const float* __restrict__
   ld_v3(st, N, t, 3, v);
   const Stencil sc = make_stencil(x, e.n, e.fn);
   const StencilAddr sa = stencil_addr(e, sc.b);
-  const float* genv = gcot + (int64_t)e.tile_off * 512 + G1;
+  const float4* genv = env_group1(e, gcot);
   const float kf = -e.dt * e.vp * 4.f * e.fn * e.fn;
   M3 A;   // times dx: offsets d in grid units below
   {
@@ -730,7 +730,7 @@ MD void p2g_adjoint_particle(const EnvDev& e, int mat, const float* __restrict__
                            (oy == 0 ? sa.y[0] : (oy == 1 ? sa.y[1] : sa.y[2]));
       float4 mP[3];
 #pragma unroll
-      for (int oz = 0; oz < 3; ++oz) mP[oz] = ld4(genv + (axy + sa.z[oz]));
+      for (int oz = 0; oz < 3; ++oz) mP[oz] = genv[axy + sa.z[oz]];
       float wx, wy, dwx, dwy;
       spline_piece(ox, sc.f[0], wx, dwx);
       spline_piece(oy, sc.f[1], wy, dwy);
@@ -828,7 +828,7 @@ MD void g2p_adjoint_body(const EnvDev& e, int mat, bool valid, uint32_t t, const
       direct_scatter<false>(e, sc, vb, Ad, 0.f, gcot);
     // x: with vg = v_i (vbar + Ad d) per node, sums of grad W vg and of W v_i, axis by axis as in gather_v
     const StencilAddr sa = stencil_addr(e, sc.b);
-    const float* genv = grid + (int64_t)e.tile_off * 512 + G1;
+    const float4* genv = env_group1(e, grid);
     float gx[3] = {0.f, 0.f, 0.f}, sv[3] = {0.f, 0.f, 0.f};
 #pragma unroll 1
     for (int ox = 0; ox < 3; ++ox) {
@@ -843,7 +843,7 @@ MD void g2p_adjoint_body(const EnvDev& e, int mat, bool valid, uint32_t t, const
         const uint32_t axy = ax + (oy == 0 ? sa.y[0] : (oy == 1 ? sa.y[1] : sa.y[2]));
         float4 v4[3];
 #pragma unroll
-        for (int oz = 0; oz < 3; ++oz) v4[oz] = ld4(genv + (axy + sa.z[oz]));
+        for (int oz = 0; oz < 3; ++oz) v4[oz] = genv[axy + sa.z[oz]];
         float wy, dwy;
         spline_piece(oy, sc.f[1], wy, dwy);
         const float d1 = (float)oy - sc.f[1];
