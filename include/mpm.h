@@ -315,9 +315,9 @@ int mpm_backward(mpm_batch* b, const float* gx, const float* gv, const float* gC
 #define MPM_OPT_GRAPHS 1       /* 1: replay each segment as a hipGraph (batched mode only; default 1) */
 #define MPM_OPT_P2G 2          /* P2G: 0 one thread per particle, global atomics; 1, 2 (default) and 3: sums per
                                   column of base cells in LDS, one global atomic per block, node and channel */
-#define MPM_OPT_G2P 3          /* 0 or 1 (default): the same kernel, gathers straight from the grid */
+#define MPM_OPT_G2P 3          /* G2P where it is not fused: 0 the plain mode's kernel, 1 (default) compiled per material */
 #define MPM_OPT_G2P_ADJ 4      /* G2P adjoint: as MPM_OPT_P2G (its scatter of node-velocity cotangents) */
-#define MPM_OPT_P2G_ADJ 5      /* 0 or 1 (default): the same kernel, gathers straight from the grid */
+#define MPM_OPT_P2G_ADJ 5      /* P2G adjoint where it is not fused: as MPM_OPT_G2P */
 #define MPM_OPT_MIN_RUN 6      /* 1 .. 256 (default 3), MPM_OPT_GRID_CAP >= 0 (default 0), MPM_OPT_MAX_RUN */
 #define MPM_OPT_GRID_CAP 7     /*   1 .. 256 (default 8): accepted and read back; no kernel depends on them */
 #define MPM_OPT_MAX_RUN 8

@@ -102,17 +102,18 @@ struct mpm_batch {
   bool last_seg_taped = false;
   std::vector<int32_t> env_err_h;
 
-  // kernel variants of the batched mode, chosen by mpm_autotune. P2G / G2P
-  // adjoint: 0 = one thread per particle with global atomics, else the column
-  // scatter. The fused schedules are the default: they read the state once per
+  // kernel variants of the batched mode, chosen by mpm_autotune. 0 = the plain
+  // mode's kernel (one thread per particle; its scatters use global atomics),
+  // else the column scatter (P2G, G2P adjoint) or the gather compiled per
+  // material (G2P, P2G adjoint). The fused schedules are the default: they read the state once per
   // substep instead of twice, and were the faster ones on every batch timed
   // (16 to 12,500 blocks, 1 to 8 particles per cell).
-  int var_p2g = 2, var_g2p_adj = 2;
+  int var_p2g = 2, var_g2p = 1, var_g2p_adj = 2, var_p2g_adj = 1;
   int box = 0;        // LDS box budget of the column scatter: 0 = 1024 nodes, 1 = 640 nodes
   int specialize = 1; // 1 = one launch per material, compiled for it; 0 = one generic launch
   int fuse = 1;       // 1: G2P of substep k and P2G of substep k + 1 in one kernel
   int fuse_adj = 1;   // 1: P2G adjoint of substep k and G2P adjoint of substep k - 1 in one kernel
-  int var_g2p = 1, var_p2g_adj = 1, min_run = 3, max_run = 8, grid_cap = 0;   // read back only
+  int min_run = 3, max_run = 8, grid_cap = 0;   // read back only
   int xcd = 0;        // 1: order each launch's items so that the blocks one XCD receives take a contiguous run
   int grid_list = 0;  // 1 / 2: the grid passes take 64 / 16 tiles per block and run only the flagged ones
   int max_col = 0;     // most colliders an env holds (slots in use): picks the grid passes' compiled variant
@@ -249,8 +250,11 @@ void batched_grid(mpm_batch* b, int gi, int clear, int k_rel) {
 
 void batched_g2p(mpm_batch* b, const float* in, float* out, int gi, int kc) {
   Span sp(b, KC_G2P);
-  for (const auto& r : launch_ranges(b))
-    launch_g2p(in, out, b->N, b->envs_d, b->items_mat_d + r.first, r.count, b->grid[gi], b->errs, kc, r.mat, b->stream);
+  if (b->var_g2p == 0)
+    launch_g2p_direct(in, out, b->N, b->envs_d, b->items_d, (int)b->items_h.size(), b->grid[gi], b->errs, kc, b->stream);
+  else
+    for (const auto& r : launch_ranges(b))
+      launch_g2p(in, out, b->N, b->envs_d, b->items_mat_d + r.first, r.count, b->grid[gi], b->errs, kc, r.mat, b->stream);
 }
 
 // G2P of substep kc from grid gi_in fused with P2G of substep kc + 1 into grid gi_out
@@ -311,8 +315,11 @@ void batched_grid_adj(mpm_batch* b, int gi, int k_rel) {
 
 void batched_p2g_adj(mpm_batch* b, const float* st, const float* cot_in, float* cot_out, int kc) {
   Span sp(b, KC_P2G_ADJ);
-  for (const auto& r : launch_ranges(b))
-    launch_p2g_adjoint(st, b->part, cot_out, b->N, b->envs_d, b->items_mat_d + r.first, r.count, b->gcot, b->pacc, kc, cot_in, r.mat, b->stream);
+  if (b->var_p2g_adj == 0)
+    launch_p2g_adjoint_direct(st, b->part, cot_out, b->N, b->envs_d, b->items_d, (int)b->items_h.size(), b->gcot, b->pacc, kc, cot_in, b->stream);
+  else
+    for (const auto& r : launch_ranges(b))
+      launch_p2g_adjoint(st, b->part, cot_out, b->N, b->envs_d, b->items_mat_d + r.first, r.count, b->gcot, b->pacc, kc, cot_in, r.mat, b->stream);
 }
 
 // P2G adjoint of substep kc (state st) fused with the G2P adjoint of substep
@@ -619,7 +626,7 @@ void* batch_stream(const mpm_batch* b) { return (void*)b->stream; }
 namespace {
 
 struct TuneChoice {
-  int p2g, g2p_adj, box, specialize, fuse, fuse_adj, xcd, grid_list;
+  int p2g, g2p, g2p_adj, p2g_adj, box, specialize, fuse, fuse_adj, xcd, grid_list;
 };
 
 // shape signature -> choice, shared by batches of the same shape in the process
@@ -636,7 +643,7 @@ std::string shape_signature(const mpm_batch* b) {
 }
 
 void apply_choice(mpm_batch* b, const TuneChoice& c) {
-  b->var_p2g = c.p2g; b->var_g2p_adj = c.g2p_adj;
+  b->var_p2g = c.p2g; b->var_g2p = c.g2p; b->var_g2p_adj = c.g2p_adj; b->var_p2g_adj = c.p2g_adj;
   b->box = c.box;
   b->specialize = c.specialize;
   b->fuse = c.fuse;
@@ -1388,8 +1395,8 @@ int mpm_autotune(mpm_batch* b, int32_t budget_ms) {
   auto over_budget = [&]() {
     return std::chrono::duration<double, std::milli>(std::chrono::steady_clock::now() - t_start).count() > budget_ms;
   };
-  // reference results: one thread per particle, global atomics
-  TuneChoice best{0, 0, 0, 1, 0, 0, 0, 0};
+  // reference results: the plain mode's kernels
+  TuneChoice best{0, 0, 0, 0, 0, 1, 0, 0, 0, 0};
   apply_choice(b, best);
   int rc = run_fwd(ref);
   if (!rc) rc = run_bwd(gref);
@@ -1407,7 +1414,7 @@ int mpm_autotune(mpm_batch* b, int32_t budget_ms) {
     ms = f;
     return MPM_OK;
   };
-  best = {2, 2, 0, 1, 1, 1, 0, 0};   // the defaults, from which one option after another is tried
+  best = {2, 1, 2, 1, 0, 1, 1, 1, 0, 0};   // the defaults, from which one option after another is tried
   // one candidate: a field of TuneChoice and its value; timed with the backward or forward only
   struct Cand { int* slot; int value; bool bwd; };
   std::vector<std::vector<Cand>> groups = {
