@@ -1332,10 +1332,10 @@ int mpm_autotune(mpm_batch* b, int32_t budget_ms) {
   if (hit != tune_cache().end()) { apply_choice(b, hit->second); return MPM_OK; }
   const hipStream_t s = b->stream;
   HIPC(b, hipStreamSynchronize(s));
-  const int64_t NS = 24 * b->N;                // floats of one state buffer
-  const int64_t R = std::max<int64_t>(b->rows, 1);
+  const int64_t NS = 24 * b->N;                // floats of one state buffer (capacity positions)
+  const int64_t R = std::max<int64_t>(b->rows, 1);   // live particles: what results are compared over
   float* saved = (float*)dalloc(b, sizeof(float) * NS);
-  float* ref = (float*)dalloc(b, sizeof(float) * NS);
+  float* ref = (float*)dalloc(b, sizeof(float) * 24 * R);
   float* cot_in = (float*)dalloc(b, sizeof(float) * 24 * R);
   float* gref = (float*)dalloc(b, sizeof(float) * 24 * R);
   float* gout = (float*)dalloc(b, sizeof(float) * 24 * R);
@@ -1369,8 +1369,7 @@ int mpm_autotune(mpm_batch* b, int32_t budget_ms) {
     restore();
     int rc = mpm_forward_envs(b, n_all.data(), 0);
     if (rc) return rc;
-    launch_copy_f32(b->cur, dst, NS, s);
-    return MPM_OK;
+    return mpm_get_particles(b, -1, dst, dst + 3 * R, dst + 6 * R, dst + 15 * R);
   };
   auto run_bwd = [&](float* dst) -> int {
     restore();
@@ -1443,7 +1442,7 @@ int mpm_autotune(mpm_batch* b, int32_t budget_ms) {
       if (c.bwd) {
         rc = rel_err(g, gref, 6 * R, err);   // x and v cotangents of the initial state
       } else {
-        rc = rel_err(g, ref, 6 * b->N, err);   // x and v of the end state
+        rc = rel_err(g, ref, 6 * R, err);   // x and v of the end state
       }
       if (rc) break;
       // a later candidate must win by more than 1%: a tie keeps the earlier (default)
