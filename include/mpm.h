@@ -348,11 +348,13 @@ int mpm_get_option(mpm_batch* b, int32_t option, int32_t* value);
 
 /* Autotuner (batched mode). Runs ckpt_every substeps from the current state
  * with every kernel variant (MPM_OPT_P2G, _G2P_ADJ, _BOX, _SPECIALIZE, _FUSE,
- * _FUSE_ADJ, _XCD, _GRID_LIST), one option at a time. A candidate is kept only if its end
- * state (x, v: relative error <= 1e-5) and its initial-state cotangent for an
- * all-ones loss cotangent (<= 1e-4) agree with the one-thread-per-particle
- * kernels; the fastest kept candidate wins, a later one only if it is more
- * than 1% faster than the choice so far. Stops trying further candidates
+ * _FUSE_ADJ, _XCD, _GRID_LIST), one option at a time from the defaults. A
+ * choice is kept only if its end state (x, v of the live particles: relative
+ * error <= 1e-5) and its initial-state cotangent for an all-ones loss
+ * cotangent (<= 1e-4) agree with the plain mode's kernels; the fastest kept
+ * one wins, a later one only if it is more than 1% faster than the choice so
+ * far. If the defaults do not agree, the unfused ones are tried, and if nothing
+ * agrees the plain mode's kernels are used. Stops trying further candidates
  * after about budget_ms milliseconds. Restores the particle state and clock,
  * drops any record, synchronizes the stream; the choice is cached per batch
  * shape for the process. Plain mode: no-op. */

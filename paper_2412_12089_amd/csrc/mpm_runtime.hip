@@ -25,6 +25,7 @@
 #include "../../include/mpm.h"
 #include "mpm_internal.h"
 #include "mpm_kernels.h"
+#include "mpm_tune.h"
 
 using namespace mpmx;
 
@@ -625,9 +626,7 @@ void* batch_stream(const mpm_batch* b) { return (void*)b->stream; }
 
 namespace {
 
-struct TuneChoice {
-  int p2g, g2p, g2p_adj, p2g_adj, box, specialize, fuse, fuse_adj, xcd, grid_list;
-};
+using mpmx::TuneChoice;
 
 // shape signature -> choice, shared by batches of the same shape in the process
 std::map<std::string, TuneChoice>& tune_cache() {
@@ -1394,14 +1393,18 @@ int mpm_autotune(mpm_batch* b, int32_t budget_ms) {
   auto over_budget = [&]() {
     return std::chrono::duration<double, std::milli>(std::chrono::steady_clock::now() - t_start).count() > budget_ms;
   };
-  // reference results: the plain mode's kernels
-  TuneChoice best{0, 0, 0, 0, 0, 1, 0, 0, 0, 0};
-  apply_choice(b, best);
+  // reference results
+  apply_choice(b, mpmx::kTuneReference);
   int rc = run_fwd(ref);
   if (!rc) rc = run_bwd(gref);
   if (!rc) HIPC(b, hipStreamSynchronize(s));
-  auto time_it = [&](bool bwd, double& ms) -> int {
-    int r = bwd ? run_bwd(g) : run_fwd(g);     // warm-up (and first-use costs)
+  // a choice agrees if the x and v of its end state and their initial cotangents match the reference's
+  auto attempt = [&](const TuneChoice& c, bool bwd, double& ms, bool& agrees) -> int {
+    apply_choice(b, c);
+    double efwd = 0.0, ebwd = 0.0;
+    int r = run_fwd(g);
+    if (!r) r = rel_err(g, ref, 6 * R, efwd);
+    if (!r && bwd) r = run_bwd(g);   // as the forward above, a first run for the timed one
     if (r) return r;
     HIPC(b, hipEventRecord(e0, s));
     r = bwd ? run_bwd(g) : run_fwd(g);
@@ -1411,49 +1414,13 @@ int mpm_autotune(mpm_batch* b, int32_t budget_ms) {
     float f = 0.f;
     HIPC(b, hipEventElapsedTime(&f, e0, e1));
     ms = f;
-    return MPM_OK;
+    if (!bwd) r = run_bwd(g);
+    if (!r) r = rel_err(g, gref, 6 * R, ebwd);
+    agrees = efwd <= 1e-5 && ebwd <= 1e-4;   // false for NaN
+    return r;
   };
-  best = {2, 1, 2, 1, 0, 1, 1, 1, 0, 0};   // the defaults, from which one option after another is tried
-  // one candidate: a field of TuneChoice and its value; timed with the backward or forward only
-  struct Cand { int* slot; int value; bool bwd; };
-  std::vector<std::vector<Cand>> groups = {
-      {{&best.p2g, 2, false}, {&best.p2g, 0, false}},
-      {{&best.g2p_adj, 2, true}, {&best.g2p_adj, 0, true}},
-      {{&best.box, 0, true}, {&best.box, 1, true}},
-      {{&best.specialize, 1, true}, {&best.specialize, 0, true}},
-      {{&best.fuse, 1, true}, {&best.fuse, 0, true}},
-      {{&best.fuse_adj, 1, true}, {&best.fuse_adj, 0, true}},
-      {{&best.xcd, 0, true}, {&best.xcd, 1, true}},
-      {{&best.grid_list, 0, true}, {&best.grid_list, 1, true}, {&best.grid_list, 2, true}},
-  };
-  for (auto& grp : groups) {
-    if (rc) break;
-    double best_ms = 1e30;
-    TuneChoice keep = best;
-    for (auto& c : grp) {
-      if (rc) break;
-      if (over_budget() && best_ms < 1e30) break;
-      TuneChoice trial = keep;
-      *(&trial.p2g + (c.slot - &best.p2g)) = c.value;
-      apply_choice(b, trial);
-      double ms = 0.0, err = 0.0;
-      rc = time_it(c.bwd, ms);
-      if (rc) break;
-      if (c.bwd) {
-        rc = rel_err(g, gref, 6 * R, err);   // x and v cotangents of the initial state
-      } else {
-        rc = rel_err(g, ref, 6 * R, err);   // x and v of the end state
-      }
-      if (rc) break;
-      // a later candidate must win by more than 1%: a tie keeps the earlier (default)
-      // choice, so timing noise does not flip between equivalent variants
-      if (err <= (c.bwd ? 1e-4 : 1e-5) && ms < best_ms * 0.99) {
-        best_ms = ms;
-        best = trial;
-      }
-    }
-    if (best_ms >= 1e30) best = keep;
-  }
+  TuneChoice best = mpmx::kTuneReference;
+  if (!rc) rc = mpmx::tune_choice(attempt, over_budget, best);
   (void)hipEventDestroy(e0);
   (void)hipEventDestroy(e1);
   restore();
