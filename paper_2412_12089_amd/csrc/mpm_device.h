@@ -239,6 +239,13 @@ MD int base_floor(float x, int n) {
   return (int)b;
 }
 
+MD void spline_weights(float f, float w[3]) {
+  const float f0 = 1.5f - f, f1 = f - 1.f, f2 = f - 0.5f;
+  w[0] = 0.5f * f0 * f0;
+  w[1] = 0.75f - f1 * f1;
+  w[2] = 0.5f * f2 * f2;
+}
+
 MD Stencil make_stencil(const float x[3], int n, float fn) {
   Stencil st;
   st.oob = false;
@@ -249,13 +256,10 @@ MD Stencil make_stencil(const float x[3], int n, float fn) {
     st.b[a] = b;
     const float f = fmaf(x[a], fn, -(float)b);
     st.f[a] = f;
-    const float f0 = 1.5f - f, f1 = f - 1.f, f2 = f - 0.5f;
-    st.w[a][0] = 0.5f * f0 * f0;
-    st.w[a][1] = 0.75f - f1 * f1;
-    st.w[a][2] = 0.5f * f2 * f2;
-    st.dw[a][0] = -f0;
-    st.dw[a][1] = -2.f * f1;
-    st.dw[a][2] = f2;
+    spline_weights(f, st.w[a]);
+    st.dw[a][0] = -(1.5f - f);
+    st.dw[a][1] = -2.f * (f - 1.f);
+    st.dw[a][2] = f - 0.5f;
   }
   return st;
 }
@@ -302,6 +306,61 @@ MHD StencilAddr stencil_addr(const EnvDev& e, const int b[3]) {
 // group 1 of the env's nodes, addressed by those offsets
 MHD const float4* env_group1(const EnvDev& e, const float* grid) {
   return reinterpret_cast<const float4*>(grid + e.tile_off * 512 + G1);
+}
+
+// a[i] for a runtime i in {0,1,2} without indexing a register array
+template <typename T>
+MD T sel3(const T a[3], int i) { return i == 0 ? a[0] : (i == 1 ? a[1] : a[2]); }
+
+// A block of 256 adds 27 nodes' worth of one particle per thread to group 0 of
+// the grid with global atomics (every thread calls it): float c of node base + o
+// gets W(o) value(r_c, (o - f) scale), r_c = (s, A[0..2]) = row[c], or with MASS
+// r_0 = (mass, 0, 0, 0) and r_c = row[c - 1]. The particles wait in LDS (pay, 4 x
+// 256 entries); a quad of lanes takes its four in turn and lane c adds float c, so
+// that one instruction adds whole groups of four floats. What bounds it are the
+// 64-byte lines that an atomic instruction touches, and one float per lane at a
+// pitch of 16 bytes touched each line once per float. Forward and backward with
+// one float per lane and now, 20 substeps: 16 dam breaks of 200,000 particles one
+// env at a time 507 -> 198 ms (390 over a grid stored one channel at a time); in
+// the batched mode's fallback, 32 envs of 9,000 particles at 0.2 per cell 61 -> 22
+// (46), 16 of 20,000 at 0.06 per cell 80 -> 28 (71).
+template <bool MASS, typename Value>
+MD void quad_scatter(const EnvDev& e, int count, const Stencil& sc, const float (&row)[3][4], float mass, float scale,
+                     Value value, float4* pay, float* __restrict__ grid) {
+  const int t = threadIdx.x, c = t & 3;
+  if (t < count) {
+    pay[t] = make_float4(sc.f[0], sc.f[1], sc.f[2], __int_as_float(sc.b[0] << 20 | sc.b[1] << 10 | sc.b[2]));   // n <= 1024
+#pragma unroll
+    for (int a = 0; a < 3; ++a) pay[(1 + a) * 256 + t] = make_float4(row[a][0], row[a][1], row[a][2], row[a][3]);
+  }
+  __syncthreads();
+  if (!MASS && c == 3) return;
+  float* base = grid + (int64_t)e.tile_off * 512 + c;
+#pragma unroll 1
+  for (int q = t & ~3; q < min((t & ~3) + 4, count); ++q) {
+    const float4 at = pay[q], rq = pay[(MASS ? max(c, 1) : 1 + c) * 256 + q];
+    const float r[4] = {MASS && c == 0 ? mass : rq.x, MASS && c == 0 ? 0.f : rq.y, MASS && c == 0 ? 0.f : rq.z,
+                        MASS && c == 0 ? 0.f : rq.w};
+    const float f[3] = {at.x, at.y, at.z};
+    const int bb = __float_as_int(at.w), b[3] = {bb >> 20, (bb >> 10) & 1023, bb & 1023};
+    float w[3][3];
+#pragma unroll
+    for (int a = 0; a < 3; ++a) spline_weights(f[a], w[a]);
+    const StencilAddr sa = stencil_addr(e, b);
+#pragma unroll 1
+    for (int ox = 0; ox < 3; ++ox)
+#pragma unroll 1
+      for (int oy = 0; oy < 3; ++oy) {
+        const float wxy = sel3(w[0], ox) * sel3(w[1], oy);
+        const float d0 = ((float)ox - f[0]) * scale, d1 = ((float)oy - f[1]) * scale;
+        float* col = base + 4 * (int64_t)(sel3(sa.x, ox) + sel3(sa.y, oy));
+#pragma unroll
+        for (int oz = 0; oz < 3; ++oz) {
+          const float d[3] = {d0, d1, ((float)oz - f[2]) * scale};
+          atomicAdd(col + 4 * (int64_t)sa.z[oz], wxy * w[2][oz] * value(r, d));
+        }
+      }
+  }
 }
 
 // --------------------------------------------------------------------------

@@ -398,7 +398,7 @@ __global__ void k_unpermute(const float* __restrict__ src, float* __restrict__ d
 }
 
 // ----------------------------------------------------------------------------
-// a3 + a4: P2G, one thread per particle, direct global atomics
+// a3 + a4: P2G, one particle per thread, direct global atomics
 // ----------------------------------------------------------------------------
 MD void mark_tiles(const EnvDev& e, const int b[3], uint32_t* __restrict__ flags) {
   const int t0[3] = {b[0] >> 2, b[1] >> 2, b[2] >> 2};
@@ -415,34 +415,29 @@ __global__ void __launch_bounds__(256) k_p2g_direct(const float* __restrict__ st
                                                     const EnvDev* __restrict__ envs,
                                                     const WorkItem* __restrict__ items, float* __restrict__ grid,
                                                     uint32_t* __restrict__ flags, int32_t* __restrict__ errs, int k_call) {
+  __shared__ float4 pay[4 * 256];
   const WorkItem it = items[blockIdx.x];
-  if ((int)threadIdx.x >= it.count) return;
+  const bool valid = (int)threadIdx.x < it.count;
   const EnvDev& e = envs[it.env];
   if (k_call >= e.nsub) return;   // frozen env: nothing to scatter
-  const int64_t p = it.start + threadIdx.x;
-  const PState s = load_state(st, N, p);
+  const PState s = load_state(st, N, it.start + (valid ? threadIdx.x : 0));
   const Stencil sc = make_stencil(s.x, e.n, e.fn);
-  if (sc.oob) atomicOr(&errs[it.env], ERR_OUT_OF_DOMAIN);
+  if (valid && sc.oob) atomicOr(&errs[it.env], ERR_OUT_OF_DOMAIN);
   const M3 tau = stress(e, s.H, e.material);
   const float kf = -e.dt * e.vp * 4.f * e.fn * e.fn;
   const M3 A = m3_axpy(m3_scale(s.C, e.mp), kf, tau);
-  mark_tiles(e, sc.b, flags);
+  if (valid) mark_tiles(e, sc.b, flags);
+  float row[3][4];
 #pragma unroll
-  for (int ox = 0; ox < 3; ++ox)
+  for (int a = 0; a < 3; ++a) {
+    row[a][0] = s.v[a];
 #pragma unroll
-    for (int oy = 0; oy < 3; ++oy)
-#pragma unroll
-      for (int oz = 0; oz < 3; ++oz) {
-        const float W = sc.w[0][ox] * sc.w[1][oy] * sc.w[2][oz];
-        const float d[3] = {((float)ox - sc.f[0]) * e.dx, ((float)oy - sc.f[1]) * e.dx, ((float)oz - sc.f[2]) * e.dx};
-        float* g = grid + node_base(e, sc.b[0] + ox, sc.b[1] + oy, sc.b[2] + oz);
-        atomicAdd(g, W * e.mp);
-#pragma unroll
-        for (int a = 0; a < 3; ++a) {
-          const float mv = e.mp * s.v[a] + A.m[a][0] * d[0] + A.m[a][1] * d[1] + A.m[a][2] * d[2];
-          atomicAdd(g + 1 + a, W * mv);
-        }
-      }
+    for (int c = 0; c < 3; ++c) row[a][1 + c] = A.m[a][c];
+  }
+  // float 0 is the mass: m_p times 1
+  quad_scatter<true>(e, it.count, sc, row, 1.f, e.dx, [&](const float r[4], const float d[3]) {
+    return e.mp * r[0] + r[1] * d[0] + r[2] * d[1] + r[3] * d[2];
+  }, pay, grid);
 }
 
 // ----------------------------------------------------------------------------
@@ -968,19 +963,20 @@ __global__ void __launch_bounds__(256) k_g2p_adjoint_direct(const float* __restr
                                                             const WorkItem* __restrict__ items,
                                                             const float* __restrict__ grid, float* __restrict__ gcot,
                                                             double* __restrict__ pacc, int k_call) {
+  __shared__ float4 pay[4 * 256];
   const WorkItem it = items[blockIdx.x];
   const bool valid = (int)threadIdx.x < it.count;
   const EnvDev& e = envs[it.env];
   if (k_call >= e.nsub) return;   // frozen env: nothing to scatter
   float pb[PB_COUNT] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+  const float D4 = 4.f * e.fn * e.fn;
+  float x[3], row[3][4];
+  load_x(st, N, it.start + (valid ? threadIdx.x : 0), x);
+  const Stencil sc = make_stencil(x, e.n, e.fn);
   if (valid) {
     const int64_t p = it.start + threadIdx.x;
-    float x[3];
-    load_x(st, N, p, x);
     const M3 H = load_m3(st, N, p, 15);
     const M3 F = f_of(H);
-    const Stencil sc = make_stencil(x, e.n, e.fn);
-    const float D4 = 4.f * e.fn * e.fn;
     // C' of the substep's output state, read from the tape (the forward's own value)
     const M3 Cn = load_cnext(st_next, N, p);
     const M3 G = m3_axpy(m3_eye(), e.dt, Cn);
@@ -993,7 +989,13 @@ __global__ void __launch_bounds__(256) k_g2p_adjoint_direct(const float* __restr
     const M3 Ftrb = project_vjp(e, Htr, Fb_in, pb, e.material);
     const M3 Cb = m3_axpy(Cb_in, e.dt, m3_mul_abt(Ftrb, F));  // C' enters F_tr = (I + dt C') F
     const M3 Fb = m3_mul_atb(G, Ftrb);
-    // pass 2: scatter to grid, accumulate dx
+#pragma unroll
+    for (int a = 0; a < 3; ++a) {
+      row[a][0] = vb[a];
+#pragma unroll
+      for (int c = 0; c < 3; ++c) row[a][1 + c] = Cb.m[a][c];
+    }
+    // accumulate dx
     for (int ox = 0; ox < 3; ++ox)
       for (int oy = 0; oy < 3; ++oy)
 #pragma unroll
@@ -1008,10 +1010,6 @@ __global__ void __launch_bounds__(256) k_g2p_adjoint_direct(const float* __restr
           float gv[3];
           for (int a = 0; a < 3; ++a)
             gv[a] = vb[a] + D4 * (Cb.m[a][0] * d[0] + Cb.m[a][1] * d[1] + Cb.m[a][2] * d[2]);
-          float* gc = gcot + nb;
-          atomicAdd(gc, W * gv[0]);
-          atomicAdd(gc + 1, W * gv[1]);
-          atomicAdd(gc + 2, W * gv[2]);
           const float vg = vi[0] * gv[0] + vi[1] * gv[1] + vi[2] * gv[2];
           for (int a = 0; a < 3; ++a) {
             const float ctv = Cb.m[0][a] * vi[0] + Cb.m[1][a] * vi[1] + Cb.m[2][a] * vi[2];
@@ -1021,6 +1019,9 @@ __global__ void __launch_bounds__(256) k_g2p_adjoint_direct(const float* __restr
     for (int a = 0; a < 3; ++a) part[a * N + p] = xb[a];
     store_m3(part, N, p, 3, Fb);
   }
+  quad_scatter<false>(e, it.count, sc, row, 0.f, e.dx, [&](const float r[4], const float d[3]) {
+    return r[0] + D4 * (r[1] * d[0] + r[2] * d[1] + r[3] * d[2]);
+  }, pay, gcot);
   block_reduce_params(pb, pacc + (int64_t)it.env * 8);
 }
 

@@ -149,9 +149,6 @@ MD void copy_rows(const float* __restrict__ src, float* __restrict__ dst, int64_
   for (int c = 0; c < 24; ++c) (dst + c * N)[t] = (src + c * N)[t];
 }
 
-// a[i] for a runtime i in {0,1,2} without indexing a register array
-MD float sel3(const float a[3], int i) { return i == 0 ? a[0] : (i == 1 ? a[1] : a[2]); }
-
 // quadratic B-spline weight of node offset o (0, 1, 2) at f = x n - base, and
 // its f-derivative: each piece is w = k (f - s)^2 + m, dw/df = 2 k (f - s). For
 // a wave-uniform o the constants are scalars and the weight costs three
@@ -514,23 +511,21 @@ MD void col_scatter(const EnvDev& e, ColShared<BOXN>& S, float mass, float* __re
   }
 }
 
-// one particle's 27 nodes added to the grid directly (a block whose boxes do not fit)
-template <bool MASS>
-MD void direct_scatter(const EnvDev& e, const Stencil& sc, const float g[3], const float A[3][3], float mass,
-                       float* __restrict__ grid) {
-#pragma unroll 1
-  for (int ox = 0; ox < 3; ++ox)
-#pragma unroll 1
-    for (int oy = 0; oy < 3; ++oy)
+// the block's particles' 27 nodes added to the grid directly (boxes that do not
+// fit): the payload rows, which hold nothing then, carry the particles
+template <bool MASS, int BOXN>
+MD void direct_scatter(const EnvDev& e, int count, ColShared<BOXN>& S, const Stencil& sc, const float g[3],
+                       const float A[3][3], float mass, float* __restrict__ grid) {
+  float row[3][4];
 #pragma unroll
-      for (int oz = 0; oz < 3; ++oz) {
-        const float W = sel3(sc.w[0], ox) * sel3(sc.w[1], oy) * sc.w[2][oz];
-        const float d[3] = {(float)ox - sc.f[0], (float)oy - sc.f[1], (float)oz - sc.f[2]};
-        float* dst = grid + node_base(e, sc.b[0] + ox, sc.b[1] + oy, sc.b[2] + oz);
-        if (MASS) atomicAdd(dst, W * mass);
-        for (int a = 0; a < 3; ++a)
-          atomicAdd(dst + MASS + a, W * (g[a] + A[a][0] * d[0] + A[a][1] * d[1] + A[a][2] * d[2]));
-      }
+  for (int a = 0; a < 3; ++a) {
+    row[a][0] = g[a];
+#pragma unroll
+    for (int c = 0; c < 3; ++c) row[a][1 + c] = A[a][c];
+  }
+  quad_scatter<MASS>(e, count, sc, row, mass, 1.f, [](const float r[4], const float d[3]) {
+    return r[0] + r[1] * d[0] + r[2] * d[1] + r[3] * d[2];
+  }, S.pay, grid);
 }
 
 // ----------------------------------------------------------------------------
@@ -659,14 +654,16 @@ MD void store_new_state(float* __restrict__ out, int64_t N, uint32_t t, const fl
 // P2G of the block's particles at positions x (every thread calls it);
 // load_rest(v, C, H) supplies the rest of a particle's state
 template <int BOXN, typename LoadRest>
-MD void p2g_col_body(const EnvDev& e, int mat, bool valid, const float x[3], LoadRest load_rest,
+MD void p2g_col_body(const EnvDev& e, int mat, int count, const float x[3], LoadRest load_rest,
                      float* __restrict__ grid, uint32_t* __restrict__ flags, int32_t* err, ColShared<BOXN>& S) {
+  const bool valid = (int)threadIdx.x < count;
   const Stencil sc = make_stencil(x, e.n, e.fn);
   if (valid && sc.oob) atomicOr(err, ERR_OUT_OF_DOMAIN);
   int pos = 0;
   const bool fits = col_index<BOXN>(e, sc.b, valid, S, pos);
+  float mv[3], Ad[3][3];
   if (valid) {
-    float v[3], mv[3], Ad[3][3];
+    float v[3];
     M3 Cm, H;
     load_rest(v, Cm, H);
     const M3 A = m3_axpy(m3_scale(Cm, e.mp), -e.dt * e.vp * 4.f * e.fn * e.fn, stress(e, H, mat));
@@ -674,14 +671,15 @@ MD void p2g_col_body(const EnvDev& e, int mat, bool valid, const float x[3], Loa
       mv[a] = e.mp * v[a];
       for (int c = 0; c < 3; ++c) Ad[a][c] = A.m[a][c] * e.dx;
     }
-    if (fits) {
+    if (fits)
       col_store(S, pos, sc, mv, Ad);
-    } else {
-      direct_scatter<true>(e, sc, mv, Ad, e.mp, grid);
+    else
       mark_particle_tiles(e, sc.b, flags);
-    }
   }
-  if (!fits) return;
+  if (!fits) {
+    direct_scatter<true>(e, count, S, sc, mv, Ad, e.mp, grid);
+    return;
+  }
   col_scatter<true, BOXN>(e, S, e.mp, grid);
   mark_run_tiles(e, S.r, flags);
 }
@@ -800,19 +798,19 @@ MD void p2g_adjoint_particle(const EnvDev& e, int mat, const float* __restrict__
 // tape's C' is the forward's own value); both and part: the block's first
 // particle's rows.
 template <int BOXN>
-MD void g2p_adjoint_body(const EnvDev& e, int mat, bool valid, uint32_t t, const float* __restrict__ st,
+MD void g2p_adjoint_body(const EnvDev& e, int mat, int count, uint32_t t, const float* __restrict__ st,
                          const float* __restrict__ st_next, int64_t N, const float cx[3], const float cv[3],
                          const M3& cC, const M3& cF, float* part, const float* __restrict__ grid, float* gcot,
                          float pb[PB_COUNT], ColShared<BOXN>& S) {
+  const bool valid = (int)threadIdx.x < count;
   float x[3];
   load_x3(st, N, t, x);
   const Stencil sc = make_stencil(x, e.n, e.fn);
   int pos = 0;
   const bool fits = col_index<BOXN>(e, sc.b, valid, S, pos);
+  float vb[3], Ad[3][3];   // Ad: 4 n^2 dx Cbar
   if (valid) {
-    float vb[3];
     for (int a = 0; a < 3; ++a) vb[a] = fmaf(e.dt, cx[a], cv[a]);
-    float Ad[3][3];   // 4 n^2 dx Cbar
     {
       const M3 H = ld_m3(st, N, t, 15);
       const M3 Cn = ld_m3(st_next, N, t, 6);
@@ -822,10 +820,7 @@ MD void g2p_adjoint_body(const EnvDev& e, int mat, bool valid, uint32_t t, const
       for (int a = 0; a < 3; ++a)
         for (int c = 0; c < 3; ++c) Ad[a][c] = 4.f * e.fn * Cb.m[a][c];
     }
-    if (fits)
-      col_store(S, pos, sc, vb, Ad);
-    else
-      direct_scatter<false>(e, sc, vb, Ad, 0.f, gcot);
+    if (fits) col_store(S, pos, sc, vb, Ad);
     // x: with vg = v_i (vbar + Ad d) per node, sums of grad W vg and of W v_i, axis by axis as in gather_v
     const StencilAddr sa = stencil_addr(e, sc.b);
     const float4* genv = env_group1(e, grid);
@@ -876,7 +871,10 @@ MD void g2p_adjoint_body(const EnvDev& e, int mat, bool valid, uint32_t t, const
       xb[a] = fmaf(e.fn, gx[a] - (Ad[0][a] * sv[0] + Ad[1][a] * sv[1] + Ad[2][a] * sv[2]), cx[a]);
     st_v3(part, N, t, 0, xb);
   }
-  if (fits) col_scatter<false, BOXN>(e, S, 0.f, gcot);
+  if (fits)
+    col_scatter<false, BOXN>(e, S, 0.f, gcot);
+  else
+    direct_scatter<false>(e, count, S, sc, vb, Ad, 0.f, gcot);
 }
 
 // ----------------------------------------------------------------------------
@@ -898,7 +896,7 @@ k_p2g_col(const float* __restrict__ st, int64_t N, const EnvDev* __restrict__ en
   st += it.start;
   float x[3];
   load_x3(st, N, t, x);
-  p2g_col_body<BOXN>(e, MAT >= 0 ? MAT : e.material, valid, x, [&](float v[3], M3& Cm, M3& H) {
+  p2g_col_body<BOXN>(e, MAT >= 0 ? MAT : e.material, it.count, x, [&](float v[3], M3& Cm, M3& H) {
     ld_v3(st, N, t, 3, v);
     Cm = ld_m3(st, N, t, 6);
     H = ld_m3(st, N, t, 15);
@@ -963,7 +961,7 @@ k_g2p2g_col(const float* __restrict__ st, float* __restrict__ out, int64_t N, co
   for (int a = 0; a < 3; ++a) xn[a] = fmaf(e.dt, vn[a], x[a]);
   if (valid) store_new_state(out, N, t, xn, vn, Cn, Hn, errs + it.env);
   if (k_call + 1 >= e.nsub) return;   // the env stops after this substep (uniform over the block)
-  p2g_col_body<BOXN>(e, mat, valid, xn, [&](float v[3], M3& Cm, M3& H) {
+  p2g_col_body<BOXN>(e, mat, it.count, xn, [&](float v[3], M3& Cm, M3& H) {
     for (int a = 0; a < 3; ++a) v[a] = vn[a];
     Cm = Cn;
     H = Hn;
@@ -991,7 +989,7 @@ k_g2p_adjoint_col(const float* __restrict__ st, const float* __restrict__ st_nex
   float cx[3], cv[3];
   ld_v3(cot, N, t, 0, cx);
   ld_v3(cot, N, t, 3, cv);
-  g2p_adjoint_body<BOXN>(e, MAT >= 0 ? MAT : e.material, valid, t, st + it.start, st_next + it.start, N, cx, cv,
+  g2p_adjoint_body<BOXN>(e, MAT >= 0 ? MAT : e.material, it.count, t, st + it.start, st_next + it.start, N, cx, cv,
                          ld_m3(cot, N, t, 6), ld_m3(cot, N, t, 15), part + it.start, grid, gcot, pb, S);
   block_reduce_params(pb, pacc + (int64_t)it.env * 8);
 }
@@ -1070,7 +1068,7 @@ k_adj_pair_col(const float* __restrict__ st_prev, const float* __restrict__ st, 
                                 cF);
     }
   }
-  g2p_adjoint_body<BOXN>(e, mat, valid, t, st_prev, st, N, cx, cv, cC, cF, part, grid_prev, gcot, pb, S);
+  g2p_adjoint_body<BOXN>(e, mat, it.count, t, st_prev, st, N, cx, cv, cC, cF, part, grid_prev, gcot, pb, S);
   block_reduce_params(pb, pacc + (int64_t)it.env * 8);
 }
 

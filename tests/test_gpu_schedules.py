@@ -3,7 +3,7 @@ import numpy as np
 import pytest
 import torch
 
-from gpu_util import make_env, random_cotangents, to_np
+from gpu_util import assert_grads, assert_state, make_env, oracle_rollout, random_cotangents, to_np
 from paper_2412_12089_amd import scenes
 
 pytestmark = pytest.mark.gpu
@@ -40,3 +40,16 @@ def test_options_at_zero_run_the_plain_kernels(material):
     zero = run([spec], 3, 2, cots, options=[(k, 0) for k in ("P2G", "G2P", "G2P_ADJ", "P2G_ADJ", "FUSE", "FUSE_ADJ")])
     for name, a, b in zip(STATE_AND_GRADS, plain, zero):
         assert np.array_equal(a, b), (name, np.abs(a - b).max())
+
+
+@pytest.mark.parametrize("N", [1, 2, 3, 5, 255, 257])
+@pytest.mark.parametrize("mode", ["plain", "batched"])
+def test_global_scatters_at_partial_quads(mode, N):
+    """The scatters with global atomics take particles in fours: counts that leave a quad partly filled, in plain mode
+    and in the batched mode's fallback (particles over the whole interior cross too many tile rows for a box)."""
+    spec = make_env(scenes.NEOHOOKEAN, N=N, n=48, seed=44, lo=0.12, side=0.76, F_dev=0.01, dt=5e-5)
+    cot = random_cotangents([spec], seed=45)
+    out = run([spec], 4, 2, cot, mode=mode)
+    o = oracle_rollout(spec, 4, cot[0])
+    assert_state(out[:4], o["state"], spec.x, f"{mode} {N}", S=4)
+    assert_grads(out[4:8], o["grads"], f"{mode} {N}")
