@@ -311,7 +311,7 @@ int mpm_backward(mpm_batch* b, const float* gx, const float* gv, const float* gC
                  float* dv0, float* dC0, float* dF0, double* dparams);
 
 /* Execution options (mpm_set_option / mpm_get_option). Changing a kernel
- * variant drops the cached graphs. */
+ * variant drops the cached graphs; options that no kernel depends on keep them. */
 #define MPM_OPT_GRAPHS 1       /* 1: replay each segment as a hipGraph (batched mode only; default 1) */
 #define MPM_OPT_P2G 2          /* P2G: 0 one thread per particle, global atomics; 1, 2 (default) and 3: sums per
                                   column of base cells in LDS, one global atomic per block, node and channel */

@@ -1281,9 +1281,9 @@ int mpm_set_option(mpm_batch* b, int32_t option, int32_t value) {
     case MPM_OPT_G2P: if (value < 0 || value > 1) break; b->var_g2p = value; drop_graphs(b); return MPM_OK;
     case MPM_OPT_G2P_ADJ: if (value < 0 || value > 3) break; b->var_g2p_adj = value; drop_graphs(b); return MPM_OK;
     case MPM_OPT_P2G_ADJ: if (value < 0 || value > 1) break; b->var_p2g_adj = value; drop_graphs(b); return MPM_OK;
-    case MPM_OPT_MIN_RUN: if (value < 1 || value > 256) break; b->min_run = value; drop_graphs(b); return MPM_OK;
-    case MPM_OPT_GRID_CAP: if (value < 0) break; b->grid_cap = value; drop_graphs(b); return MPM_OK;
-    case MPM_OPT_MAX_RUN: if (value < 1 || value > 256) break; b->max_run = value; drop_graphs(b); return MPM_OK;
+    case MPM_OPT_MIN_RUN: if (value < 1 || value > 256) break; b->min_run = value; return MPM_OK;
+    case MPM_OPT_GRID_CAP: if (value < 0) break; b->grid_cap = value; return MPM_OK;
+    case MPM_OPT_MAX_RUN: if (value < 1 || value > 256) break; b->max_run = value; return MPM_OK;
     case MPM_OPT_BOX: if (value < 0 || value > 1) break; b->box = value; drop_graphs(b); return MPM_OK;
     case MPM_OPT_SPECIALIZE: if (value < 0 || value > 1) break; b->specialize = value; drop_graphs(b); return MPM_OK;
     case MPM_OPT_FUSE: if (value < 0 || value > 1) break; b->fuse = value; drop_graphs(b); return MPM_OK;
