@@ -23,19 +23,19 @@
 //     plain 128-bit reads and writes do;
 //  5. each box node goes to the grid once, four lanes per node.
 //
-// Measured, us per launch, on 3.2 M water particles (16 envs, 96^3, 0.9 per cell), 640,000
-// corotated (32 envs, 48^3, 8 per cell) and 320,000 von Mises (128 envs, 48^3, 8 per
-// cell); before: a scatter per box node or per cell, with LDS copies of the grid
-// for the gathers, over a grid stored one channel at a time:
+// Measured, us per launch, on 3.2 M water particles (16 envs, 96^3, 0.9 per cell, large
+// box), 640,000 corotated (32 envs, 48^3, 8 per cell, small box) and 320,000 von Mises
+// (128 envs, 48^3, 8 per cell, small box); before: a scatter per box node or per cell,
+// with LDS copies of the grid for the gathers, over a grid stored one channel at a time:
 //                 water          corotated      von Mises
-//   P2G           353 -> 240     63 -> 52       53 -> 35
-//   G2P           222 -> 126     25 -> 22.5     20 -> 19
-//   G2P + P2G     462 -> 289     71 -> 61       63 -> 46
-//   G2P adjoint   514 -> 344     71 -> 60       68 -> 50
-//   P2G adjoint   326 -> 195     65 -> 44       50 -> 35
-//   adjoint pair  749 -> 441     114 -> 89      100 -> 75
-// What bounds them now: at 8 per cell instruction issue (the vector ALUs are busy 67%
-// of a G2P + P2G and 75% of a pair, the rest is the scatter's chain of barriers); at
+//   P2G           353 -> 241     63 -> 52.5     53 -> 34
+//   G2P           222 -> 133     25 -> 21.5     20 -> 18.5
+//   G2P + P2G     462 -> 289     71 -> 60       63 -> 45
+//   G2P adjoint   514 -> 356     71 -> 61       68 -> 48
+//   P2G adjoint   326 -> 208     65 -> 43       50 -> 34
+//   adjoint pair  749 -> 453     114 -> 88      100 -> 72.5
+// What bounds them now: at 8 per cell instruction issue (the vector ALUs are busy 72%
+// of a G2P + P2G and 78% of a pair, the rest is the scatter's chain of barriers); at
 // one per cell the box flush, 2.75 million 64-byte lines of global atomics per
 // launch at the chip's 20 per ns, 137 us, which the rest overlaps in part.
 #include "mpm_kernels.h"
@@ -50,13 +50,17 @@ constexpr int kBins = 8;           // task lengths told apart
 // and room for base cells (a block with more adds to the grid directly). The
 // larger pair leaves four blocks per CU (LDS) and holds a box of 28 z nodes
 // across a whole tile row. The smaller one with its 96 VGPRs leaves five (32,000
-// bytes of LDS is the most for that): the scatter's barriers and LDS chains want
-// the fifth where the boxes fit. G2P + P2G, 640,000 corotated particles (32
-// envs, 48^3, 8 per cell) 65.8 -> 60.9 us, 320,000 von Mises (128 envs, 48^3, 8
-// per cell) 53 -> 46; where they do not, at one particle per cell, the second
-// pass costs more: 3.2 M water particles (16 envs, 96^3) 289 -> 298. (384 nodes
-// with six blocks lost to one of the two at each of these.) The autotuner
-// measures both.
+// bytes of LDS is the most for that) to all but the adjoint pair, whose 128 VGPRs
+// allow four: the scatter's barriers and LDS chains want the fifth where the boxes
+// fit. From large to small, us: P2G and G2P + P2G of 640,000 corotated particles (32
+// envs, 48^3, 8 per cell) 56 -> 52.5 and 64 -> 60, of 320,000 von Mises (128 envs,
+// 48^3, 8 per cell) 41 -> 34 and 51 -> 45; where they do not fit, at one particle per
+// cell, the second pass costs more: 3.2 M water particles (16 envs, 96^3) 241 -> 258
+// and 288 -> 294. The G2P adjoint follows its registers too: water 357 -> 336,
+// corotated 65 -> 62, but a batch of three materials 252 -> 267 (its von Mises form
+// spills). The pair differs by spills and passes alone: water 449 -> 467, the others
+// within 1%. (384 nodes with six blocks lost to one of the two at each of these.)
+// The autotuner measures both and takes one for all four kernels.
 constexpr int kBoxLarge = 1024;
 constexpr int kBoxSmall = 640;
 template <int BOXN>
@@ -591,7 +595,8 @@ MD void gather_v_nested(const EnvDev& e, const float* __restrict__ grid, const f
 // seeds) two runs of one build differ there by 1.2e-5 to 2.5e-5; against the
 // kernels that staged boxes in LDS, which summed in this order, the nested sums
 // differed by 3.1 times that (4.4 in the worst seed) and these differ by 1.7 times
-// (2.2). The fluid's scatter hides the products: 121.2 ms a pass either way.
+// (2.2). The fluid's scatter hides the products: G2P + P2G 287.5 -> 288.7 us, the
+// whole pass 121 ms either way (k_g2p alone 128 -> 133 us).
 MD void gather_v_flat(const EnvDev& e, const float* __restrict__ grid, const float x[3], float vn[3], M3& Cn) {
   const Stencil sc = make_stencil(x, e.n, e.fn);
   const StencilAddr sa = stencil_addr(e, sc.b);
@@ -905,7 +910,7 @@ k_p2g_col(const float* __restrict__ st, int64_t N, const EnvDev* __restrict__ en
 
 // G2P: 27 128-bit node reads per particle straight from the grid. Neighbouring
 // lanes read the same lines, which the L1 serves: staging boxes in LDS first took
-// 222 us where this takes 126 (3.2 M water particles; 3.7 TB/s of state alone).
+// 222 us where this takes 133 (3.2 M water particles; 3.5 TB/s of state alone).
 template <int MAT>
 __global__ void __launch_bounds__(256) k_g2p(const float* __restrict__ st, float* __restrict__ out, int64_t N,
                                              const EnvDev* __restrict__ envs, const WorkItem* __restrict__ items,
@@ -969,8 +974,8 @@ k_g2p2g_col(const float* __restrict__ st, float* __restrict__ out, int64_t N, co
 }
 
 // G2P adjoint. Its gather of v and its payload share the particle's registers, so
-// the corotated and von Mises forms spill a little at five blocks per CU and are
-// still faster there (67 -> 60 us, 640,000 corotated particles).
+// the von Mises form spills a little at five blocks per CU and is still faster there
+// on equal envs (50 -> 47 us, 320,000 particles; corotated, without spills, 65 -> 62).
 template <int BOXN, int MAT>
 __global__ void __launch_bounds__(256, waves_per_simd<BOXN>())
 k_g2p_adjoint_col(const float* __restrict__ st, const float* __restrict__ st_next,
@@ -996,7 +1001,7 @@ k_g2p_adjoint_col(const float* __restrict__ st, const float* __restrict__ st_nex
 
 // P2G adjoint: a gather of (mbar, Pbar) and the stress VJP; issue-bound. Four waves per
 // SIMD; the nodes are summed flat per (x, y) column, since sums nested per axis keep
-// more registers live and spill (640,000 corotated particles: 54 us nested, 44 flat).
+// more registers live and spill (640,000 corotated particles: 54 us nested, 43 flat).
 template <int MAT>
 __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4, 8)))
 k_p2g_adjoint(const float* __restrict__ st, const float* __restrict__ part, float* __restrict__ cot_out, int64_t N,
